@@ -162,6 +162,29 @@ def test_rounds_bit_exact(name, n_prog, s_max, F, depth, p_nan, rounds):
     np.testing.assert_array_equal(gm.view(np.uint32), wm.view(np.uint32))
 
 
+@pytest.mark.parametrize("name,n_prog,s_max,F,depth,p_nan,min_rows", [
+    # rows just above the sets evaluated in place: several chunks, kept and derived histograms
+    ("one group", 1400, 5, 3, 7, 0.0, 4097),
+    ("ragged groups, missing values", 6000, 9, 13, 8, 0.3, 25000),
+    # so many feature groups that a level is cut into two chunks only
+    ("most features", 1500, 5, 4096, 3, 0.1, 4097),
+])
+def test_histogram_routes_bit_exact(name, n_prog, s_max, F, depth, p_nan, min_rows):
+    require_gpu()
+    cfg = mini_config(n_prog=n_prog, s_max=s_max, n_features=F, p_nan=p_nan, seed=depth, n_calib=512)
+    m = _case(cfg, 254 if F < 100 else 30)
+    assert m["n_rows"] >= min_rows
+    bins = oracle.gbdt_bin_np(m["features"], m["n_rows"], m["cuts"], m["n_cuts"], _ld(F))
+    m0 = np.zeros(m["n_rows"], np.float32)
+    kw = dict(max_depth=depth, gamma=0.0, reg_lambda=1.0, eta=0.3)
+    log("gbdt histogram routes: %s rows=%d F=%d depth=%d" % (name, m["n_rows"], F, depth))
+    got, gm = gpu_rounds(bins, F, m["cuts"], m["n_cuts"], m["prog_ptr"], m["label"], m["weight"], m0, 1, **kw)
+    want, wm = oracle_rounds(bins, F, m["cuts"], m["n_cuts"], m["prog_ptr"], m["label"], m["weight"], m0, 1, **kw)
+    assert int((want[0]["feature"] >= 0).sum()) >= 3
+    assert_trees_equal(got, want, name)
+    np.testing.assert_array_equal(gm.view(np.uint32), wm.view(np.uint32))
+
+
 def test_standard_measured_set_bit_exact():
     """4,096 measured programs of U{1..32} statements (66,923 rows), 164 features, 254 cut points,
     Ansor's settings (depth 10, eta 0.2, gamma 0.001): two rounds."""
