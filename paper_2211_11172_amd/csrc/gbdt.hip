@@ -68,7 +68,7 @@ constexpr int kManyRows = 1 << 20;   // sets from this size: more chunks, 16 row
 constexpr int kMaxChunksInFlight = 98;  // histogram workgroups per feature group, at most
 constexpr int64_t kLineBytes = 96 << 20;  // bin bytes from which rows are laid out in lines
 constexpr int kQProgs = 32;          // programs per k_gb_row_q workgroup
-constexpr int kBinRowBlocks = 8;     // at most this many 256-row blocks per binning workgroup
+constexpr int kBinPasses = 16;       // passes over rows per binning workgroup, at most
 
 struct Params {
     double eta, lambda, gamma, mcw, base;
@@ -162,41 +162,130 @@ __device__ __forceinline__ void best_lanes(int &bv, double &bg, int &bk, int64_t
 // ------------------------------------------------------------------------------------------
 // binning
 // ------------------------------------------------------------------------------------------
-// Thread = (row, 8-feature group); the group's cut points are staged in LDS first, so the binary
-// searches run on LDS, and each workgroup then bins rb_per blocks of 256 rows with them.
+// Workgroup = (8-feature group, range of rows).  Per feature a table of 256 buckets of the cut points'
+// order-preserving keys is built in LDS first: bucket -> how many cut points lie in lower buckets and
+// how many up to it, so a value starts its binary search with the cut points of its own bucket alone
+// (`steps` probes, for the fullest bucket of the group: 2 for cut points spread over the keys, 8 at
+// most).  The bucket is any monotone function of the key, the same for cut points and values, so the
+// result is the plain count of cut points <= x; -0 counts as +0.  A thread codes two rows of the
+// group, whose 16 searches overlap.
+// 2.12 M rows x 164 features: 790 us with searches over all cut points (8 probes), 460 us now, 3.8
+// TB/s of the features and bins; the probes' LDS reads and the address arithmetic bound it.
+__device__ __forceinline__ uint32_t bin_key(float v) {
+    const uint32_t u = __float_as_uint(v + 0.f);  // -0 + 0 = +0
+    return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+}
+
+__device__ __forceinline__ uint32_t bin_bucket(float v, uint32_t base, int sh) {
+    const uint32_t k = bin_key(v), d = k > base ? k - base : 0u;
+    return min(d >> sh, 255u);
+}
+
+constexpr int kBinRows = 2;          // rows per thread and pass
+constexpr int kCutStride = 264;      // cut points per feature in LDS: NaN past the last one
+
 __global__ __launch_bounds__(kThreads) void k_gb_bin(const float *__restrict__ x, int64_t ldx, int F, int N,
                                                      const float *__restrict__ cuts, int cut_stride,
                                                      const int32_t *__restrict__ n_cuts, uint8_t *__restrict__ bins,
-                                                     int64_t ld, int rb_per) {
-    __shared__ float sc[kGroup][256];
-    __shared__ int snc[kGroup];
+                                                     int64_t ld, int passes) {
+    __shared__ float sc[kGroup][kCutStride];
+    __shared__ uint16_t lut[kGroup][256];  // cut points in lower buckets | up to this one << 8
+    __shared__ uint8_t cb[kGroup][256];    // bucket of every cut point
+    __shared__ int snc[kGroup], ssh[kGroup], full;
+    __shared__ uint32_t sbase[kGroup];
     const int g = blockIdx.y, t = threadIdx.x;
-    if (t < kGroup) snc[t] = g * kGroup + t < F ? clamp_cuts(n_cuts, g * kGroup + t, cut_stride) : 0;
+    const int nf = min(kGroup, F - g * kGroup);
+    if (t < kGroup) {
+        const int nc = t < nf ? clamp_cuts(n_cuts, g * kGroup + t, cut_stride) : 0;
+        snc[t] = nc;
+        uint32_t base = 0;
+        int sh = 0;
+        if (nc > 0) {
+            const float *c = cuts + (int64_t)(g * kGroup + t) * cut_stride;
+            const uint32_t k0 = bin_key(c[0]), k1 = bin_key(c[nc - 1]), span = k1 > k0 ? k1 - k0 : 0u;
+            while ((span >> sh) > 253u) ++sh;
+            base = k0 > (1u << sh) ? k0 - (1u << sh) : 0u;  // the first cut point in bucket 1
+        }
+        sbase[t] = base;
+        ssh[t] = sh;
+    }
+    if (t == 0) full = 0;
     __syncthreads();
-    for (int e = t; e < kGroup * 256; e += kThreads) {
-        const int j = e / 256, i = e % 256;
-        if (i < snc[j]) sc[j][i] = cuts[(int64_t)(g * kGroup + j) * cut_stride + i];
+    for (int e = t; e < kGroup * kCutStride; e += kThreads) {
+        const int j = e / kCutStride, i = e % kCutStride;
+        const float v = i < snc[j] ? cuts[(int64_t)(g * kGroup + j) * cut_stride + i] : NAN;
+        sc[j][i] = v;
+        if (i < snc[j]) cb[j][i] = (uint8_t)bin_bucket(v, sbase[j], ssh[j]);
     }
     __syncthreads();
-    for (int rb = 0; rb < rb_per; ++rb) {
-        const int r = (blockIdx.x * rb_per + rb) * kThreads + t;
-        if (r >= N) return;
-        uint64_t word = 0;
-#pragma unroll
-        for (int j = 0; j < kGroup; ++j) {
-            const int f = g * kGroup + j;
-            if (f >= F) break;
-            const float v = x[(int64_t)f * ldx + r];
-            int lo = 0, hi = snc[j];
-            while (lo < hi) {  // number of cut points <= v
-                const int mid = (lo + hi) >> 1;
-                if (sc[j][mid] <= v) lo = mid + 1;
-                else hi = mid;
-            }
-            const uint64_t b = v != v ? 255u : (uint64_t)lo;
-            word |= b << (8 * j);
+    int most = 0;
+#pragma unroll 1
+    for (int j = 0; j < nf; ++j) {  // thread t: bucket t
+        int lo = 0, hi = snc[j];
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (cb[j][mid] < t) lo = mid + 1;
+            else hi = mid;
         }
-        *reinterpret_cast<uint64_t *>(bins + ((int64_t)g * ld + r) * kGroup) = word;
+        int up = lo, top = snc[j];
+        while (up < top) {
+            const int mid = (up + top) >> 1;
+            if (cb[j][mid] <= t) up = mid + 1;
+            else top = mid;
+        }
+        lut[j][t] = (uint16_t)(lo | up << 8);
+        most = max(most, up - lo);
+    }
+    if (most > 0) atomicMax(&full, most);
+    __syncthreads();
+    const int steps = 32 - __builtin_clz(full | 1) - (full == 0);  // 2^steps > full
+    uint32_t base[kGroup];
+    int sh[kGroup];
+#pragma unroll
+    for (int j = 0; j < kGroup; ++j) {
+        base[j] = sbase[j];
+        sh[j] = ssh[j];
+    }
+    const float *__restrict__ xg = x + (int64_t)g * kGroup * ldx;
+    for (int ps = 0; ps < passes; ++ps) {
+        const int r0 = (blockIdx.x * passes + ps) * kThreads * kBinRows + t;
+        if (r0 - t >= N) return;
+        float v[kBinRows][kGroup];
+        int lo[kBinRows][kGroup], hi[kBinRows][kGroup];
+#pragma unroll
+        for (int q = 0; q < kBinRows; ++q)
+#pragma unroll
+            for (int j = 0; j < kGroup; ++j)  // clamped: rows past N and features past F are not stored
+                v[q][j] = xg[(int64_t)min(j, nf - 1) * ldx + min(r0 + q * kThreads, N - 1)];
+#pragma unroll
+        for (int q = 0; q < kBinRows; ++q)
+#pragma unroll
+            for (int j = 0; j < kGroup; ++j) {
+                const uint32_t e = lut[j][bin_bucket(v[q][j], base[j], sh[j])];
+                lo[q][j] = (int)(e & 255u);
+                hi[q][j] = (int)(e >> 8);
+            }
+        for (int s = 0; s < steps; ++s)  // a finished search stays: its next cut point is > v (or the NaN after the last)
+#pragma unroll
+            for (int q = 0; q < kBinRows; ++q)
+#pragma unroll
+                for (int j = 0; j < kGroup; ++j) {
+                    const int mid = (lo[q][j] + hi[q][j]) >> 1;
+                    const bool up = sc[j][mid] <= v[q][j];
+                    lo[q][j] = up ? mid + 1 : lo[q][j];
+                    hi[q][j] = up ? hi[q][j] : mid;
+                }
+#pragma unroll
+        for (int q = 0; q < kBinRows; ++q) {
+            uint32_t w[2] = {0, 0};
+#pragma unroll
+            for (int j = 0; j < kGroup; ++j) {
+                const uint32_t b = v[q][j] != v[q][j] ? 255u : (uint32_t)min(lo[q][j], 254);
+                if (j < nf) w[j / 4] |= b << (8 * (j % 4));
+            }
+            const int r = r0 + q * kThreads;
+            if (r < N) *reinterpret_cast<uint2 *>(bins + ((int64_t)g * ld + r) * kGroup) = make_uint2(w[0], w[1]);
+        }
     }
 }
 
@@ -1142,12 +1231,12 @@ int gbdt_bin_launch(const float *x, int64_t ldx, int32_t F, int32_t N, const flo
                     const int32_t *n_cuts, uint8_t *bins, int64_t ld, hipStream_t stream) {
     if (N == 0) return HARL_OK;
     // bytes of features past F in the last group are written as zeros
-    // several row blocks per cut staging on large sets, while keeping about 2,048 workgroups
-    const int64_t n_g = ceil_div(F, kGroup);
-    const int rb_per = (int)std::max<int64_t>(1, std::min<int64_t>(kBinRowBlocks, ceil_div(N, kThreads) * n_g / 2048));
-    const dim3 grid((unsigned)ceil_div(N, kThreads * rb_per), (unsigned)n_g);
+    // several passes per table on large sets, while keeping about 768 workgroups
+    const int64_t n_g = ceil_div(F, kGroup), per = kThreads * kBinRows;
+    const int passes = (int)std::max<int64_t>(1, std::min<int64_t>(kBinPasses, ceil_div(N, per) * n_g / 768));
+    const dim3 grid((unsigned)ceil_div(N, per * passes), (unsigned)n_g);
     hipLaunchKernelGGL(k_gb_bin, grid, dim3(kThreads), 0, stream, x, ldx, F, N, cuts, cut_stride, n_cuts, bins, ld,
-                       rb_per);
+                       passes);
     HARL_HIP_CHECK(hipGetLastError());
     return HARL_OK;
 }
