@@ -16,14 +16,18 @@
 //    and lane shuffles up to one key per thread).  Lanes of one LDS atomic that hit
 //    the same address are serialised, so histogram updates and compaction slots are aggregated per
 //    wave first.
-//    Segments run in parallel; their selections (unsorted: the next round selects again) form the
-//    next round's candidates until one segment is left, whose workgroup writes the final top-k
-//    directly (or, sorted, for the merge).
-// K5 k_topk_merge: merges the sorted top-k of this call into the sorted running top-k by rank
-//    computation (an element's output slot is its own index plus the number of elements of the
-//    other list that rank ahead of it).
+//    Candidates to be merged into a running list are dropped at the load unless they rank ahead of
+//    its last entry (after the first batches of a stream few do, and a segment of at most kk needs no
+//    radix pass).  Segments run in parallel; while there are more than kMaxLists of them (or than
+//    their keys fit LDS) their selections, unsorted, form the next round's candidates.  The last
+//    round sorts its lists; a single one is written out or merged by K5.
+// K4 k_topk_rank: the top k of several sorted lists and the running list by rank computation (an
+//    element's output slot is its own place plus the number of elements of every other list that rank
+//    ahead of it), a workgroup per 1,024 elements.
+// K5 k_topk_merge: merges one sorted list of this call into the sorted running top-k, likewise.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "internal.hpp"
@@ -42,6 +46,7 @@ constexpr int kPerThread = 8;
 constexpr int kRankSortMax = 128;  // up to this many selected keys are ranked directly, else bitonic
 constexpr int kSeg = kSelThreads * kPerThread;  // candidates per workgroup
 constexpr int kMergeThreads = 1024;
+constexpr int kMaxLists = 16, kListKeys = 16384;  // sorted lists k_topk_rank takes, and their keys in LDS
 
 __device__ __forceinline__ uint32_t order_key(float s) {
     uint32_t b = __float_as_uint(s);
@@ -62,23 +67,54 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v, int lane) {
     return v;
 }
 
+// a ranks ahead of b
+__device__ __forceinline__ bool ahead(uint32_t ka, int64_t ia, uint32_t kb, int64_t ib) {
+    return ka > kb || (ka == kb && ia < ib);
+}
+
+// What a selection kernel (RUN) needs of a running top-k that its candidates will be merged into: a
+// candidate that does not rank ahead of the running list's last entry cannot enter it and is dropped
+// at the load; workgroup 0 copies the list to where k_topk_rank, which rewrites it from several
+// workgroups, reads it.
+struct Running {
+    const float *score;
+    const int64_t *index;
+    int k;
+    int64_t index_base;
+    float *score_copy;     // null: no copy
+    int64_t *index_copy;
+};
+
 // FROM_SCORES: round 0 reads fp32 scores (candidate = position); later rounds read composites.
 // emit: this is the last round and its (single) workgroup writes io_score / io_index directly.
-// sort_out: the kk selected composites are written in rank order (the last round, whose list is
+// sort_out: the kk selected composites are written in rank order (the last round, whose lists are
 // emitted or merged); the rounds before it feed another selection, which needs no order.
-template <bool FROM_SCORES>
+// counts: with sort_out, the number of candidates at the head of each list (the rest is zeros).
+template <bool FROM_SCORES, bool RUN>
 __global__ __launch_bounds__(kSelThreads) void k_topk_select(const float *__restrict__ score, const uint64_t *__restrict__ cin,
                                                              int64_t count, int kk, uint64_t *__restrict__ cout, int emit,
                                                              int sort_out, int n, int64_t index_base,
-                                                             float *__restrict__ out_score, int64_t *__restrict__ out_index) {
+                                                             float *__restrict__ out_score, int64_t *__restrict__ out_index,
+                                                             int32_t *__restrict__ counts, Running run) {
     __shared__ uint32_t hist[2][256];  // digit histograms of consecutive passes (one is cleared meanwhile)
     __shared__ uint64_t sel[HARL_TOPK_MAX_K > kRankSortMax ? HARL_TOPK_MAX_K : kRankSortMax];
     __shared__ uint64_t ranked[kRankSortMax];
-    __shared__ uint32_t s_digit, s_above, s_eq, s_cnt;
+    __shared__ uint32_t s_digit, s_above, s_eq, s_cnt, s_valid[kSelThreads / 64];
     const int t = threadIdx.x, lane = t % 64;
     const int64_t base = (int64_t)blockIdx.x * kSeg;
     const int64_t rem = count - base;
-    const int n_valid = rem < kSeg ? (int)rem : kSeg;
+    const int n_here = rem < kSeg ? (int)rem : kSeg;
+    if (RUN && run.score_copy && blockIdx.x == 0)
+        for (int i = t; i < run.k; i += kSelThreads) {
+            run.score_copy[i] = run.score[i];
+            run.index_copy[i] = run.index[i];
+        }
+    uint32_t last_key = 0;
+    int64_t last_index = INT64_MAX;
+    if (FROM_SCORES && RUN) {
+        last_key = order_key(run.score[run.k - 1]);
+        last_index = run.index[run.k - 1];
+    }
 
     uint64_t x[kPerThread];
 #pragma unroll
@@ -86,18 +122,33 @@ __global__ __launch_bounds__(kSelThreads) void k_topk_select(const float *__rest
         const int64_t i = base + (int64_t)j * kSelThreads + t;
         x[j] = 0;  // padding ranks below every candidate and never enters a histogram
         if (i < count) {
-            if constexpr (FROM_SCORES)
-                x[j] = ((uint64_t)order_key(score[i]) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)i);
-            else
+            if constexpr (FROM_SCORES) {
+                const uint32_t key = order_key(score[i]);
+                if (!RUN || ahead(key, run.index_base + i, last_key, last_index))
+                    x[j] = ((uint64_t)key << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)i);
+            } else {
                 x[j] = cin[i];
+            }
         }
     }
     // register slots j >= jn hold no candidate in any thread: the loops below skip them uniformly
-    const int jn = (n_valid + kSelThreads - 1) / kSelThreads;
-    auto valid = [&](int j) { return j * kSelThreads + t < n_valid; };
+    const int jn = (n_here + kSelThreads - 1) / kSelThreads;
+    auto valid = [&](int j) { return RUN ? x[j] != 0 : j * kSelThreads + t < n_here; };  // no candidate's composite is 0
+    if constexpr (RUN) {  // candidates were dropped: count the others
+        uint32_t mine = 0;
+#pragma unroll
+        for (int j = 0; j < kPerThread; ++j) mine += (uint32_t)__popcll(__ballot(x[j] != 0));
+        if (lane == 0) s_valid[t / 64] = mine;
+    }
     for (int i = t; i < 2 * 256; i += kSelThreads) (&hist[0][0])[i] = 0;
     if (t == 0) s_cnt = 0;
     __syncthreads();
+    int n_valid = n_here;
+    if constexpr (RUN) {
+        n_valid = 0;
+#pragma unroll
+        for (int v = 0; v < kSelThreads / 64; ++v) n_valid += (int)s_valid[v];
+    }
 
     // ---- radix select: find the prefix of the kk-th largest composite ----
     uint64_t prefix = 0;
@@ -219,7 +270,7 @@ __global__ __launch_bounds__(kSelThreads) void k_topk_select(const float *__rest
         // 2, at most one per thread): a thread holds one key; partners fewer than 64 positions away
         // are in its wave and exchange by lane shuffles, the others through LDS (two barriers)
         int P = 1;
-        while (P < kk) P <<= 1;
+        while (P < min(kk, n_valid)) P <<= 1;  // a short list is zeros past its candidates
         for (int i = kk + t; i < P; i += kSelThreads) sel[i] = 0;
         __syncthreads();
         uint64_t key = t < P ? sel[t] : 0;
@@ -244,7 +295,7 @@ __global__ __launch_bounds__(kSelThreads) void k_topk_select(const float *__rest
         __syncthreads();
     } else {
         int P = 1;
-        while (P < kk) P <<= 1;
+        while (P < min(kk, n_valid)) P <<= 1;
         for (int i = kk + t; i < P; i += kSelThreads) sel[i] = 0;
         __syncthreads();
         // bitonic sort of the kk selected composites, descending
@@ -263,6 +314,7 @@ __global__ __launch_bounds__(kSelThreads) void k_topk_select(const float *__rest
             }
         }
     }
+    if (sort_out && counts && t == 0) counts[blockIdx.x] = min(n_valid, kk);
     for (int i = t; i < kk; i += kSelThreads) {
         const uint64_t key = out_keys[i];
         if (emit) {
@@ -276,19 +328,16 @@ __global__ __launch_bounds__(kSelThreads) void k_topk_select(const float *__rest
     }
 }
 
-// a ranks ahead of b
-__device__ __forceinline__ bool ahead(uint32_t ka, int64_t ia, uint32_t kb, int64_t ib) {
-    return ka > kb || (ka == kb && ia < ib);
-}
-
 // running (k sorted entries in io_*) <- top-k of running U batch (nb sorted composites of this call).
-__global__ __launch_bounds__(kMergeThreads) void k_topk_merge(const uint64_t *__restrict__ bkeys, int nb,
+__global__ __launch_bounds__(kMergeThreads) void k_topk_merge(const uint64_t *__restrict__ bkeys,
+                                                              const int32_t *__restrict__ count,
                                                               const float *__restrict__ score, int n, int64_t index_base,
                                                               float *__restrict__ io_score, int64_t *__restrict__ io_index,
                                                               int k) {
     __shared__ uint32_t ak[HARL_TOPK_MAX_K], bk[HARL_TOPK_MAX_K];
     __shared__ int64_t ai[HARL_TOPK_MAX_K], bi[HARL_TOPK_MAX_K];
     __shared__ float as[HARL_TOPK_MAX_K], bs[HARL_TOPK_MAX_K];
+    const int nb = min(max(*count, 0), k);
     for (int i = threadIdx.x; i < k; i += kMergeThreads) {
         as[i] = io_score[i];
         ak[i] = order_key(as[i]);
@@ -329,6 +378,105 @@ __global__ __launch_bounds__(kMergeThreads) void k_topk_merge(const uint64_t *__
             io_score[pos] = bs[j];
             io_index[pos] = bi[j];
         }
+    }
+}
+
+// The top k of up to kMaxLists sorted lists of composites (list q: `counts[q]` of its kk slots) and, with
+// run_score, of the copy of a running top-k: an element's output slot is its place in its own list plus
+// the number of elements ahead of it in every other one, by binary search.  All lists lie in LDS;
+// workgroup b ranks elements [1024 b, 1024 b + 1024) of the lists' slots in turn, then of the running
+// list.  Equal entries cannot meet within the lists, and the running list's come first.
+__global__ __launch_bounds__(kMergeThreads) void k_topk_rank(const uint64_t *__restrict__ lists,
+                                                             const int32_t *__restrict__ counts, int n_lists, int kk,
+                                                             const float *__restrict__ score, int n, int64_t index_base,
+                                                             const float *__restrict__ run_score,
+                                                             const int64_t *__restrict__ run_index, int k,
+                                                             float *__restrict__ out_score, int64_t *__restrict__ out_index) {
+    extern __shared__ __align__(16) char smem[];
+    __shared__ int cnt[kMaxLists];
+    uint64_t *keys = reinterpret_cast<uint64_t *>(smem);                // [n_lists][kk]
+    int64_t *ri = reinterpret_cast<int64_t *>(keys + n_lists * kk);     // running list: indices, order keys
+    uint32_t *rk = reinterpret_cast<uint32_t *>(ri + k);
+    const int t = threadIdx.x;
+    if (t < n_lists) cnt[t] = min(max(counts[t], 0), kk);
+    for (int i0 = t; i0 < n_lists * kk; i0 += 8 * kMergeThreads) {  // eight loads in flight
+        uint64_t v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = lists[min(i0 + u * kMergeThreads, n_lists * kk - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (i0 + u * kMergeThreads < n_lists * kk) keys[i0 + u * kMergeThreads] = v[u];
+    }
+    if (run_score)
+        for (int i = t; i < k; i += kMergeThreads) {
+            rk[i] = order_key(run_score[i]);
+            ri[i] = run_index[i];
+        }
+    __syncthreads();
+    int steps = 0;
+    while ((1 << steps) <= kk) ++steps;  // 2^steps > kk: a search over a list ends within `steps` probes
+    const int per_list = (kk + kMergeThreads - 1) / kMergeThreads;
+    const int own = (int)blockIdx.x / per_list;
+    if (own < n_lists) {
+        const int p = (int)blockIdx.x % per_list * kMergeThreads + t;
+        if (p >= cnt[own]) return;
+        const uint64_t key = keys[own * kk + p];
+        int pos = p;
+        // four searches at a time: their probes overlap
+        for (int q0 = 0; q0 < n_lists; q0 += 4) {
+            int lo[4], hi[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int q = q0 + u;
+                lo[u] = 0;
+                hi[u] = q < n_lists && q != own ? cnt[q] : 0;
+            }
+            for (int s = 0; s < steps; ++s)
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (lo[u] < hi[u]) {
+                        const int mid = (lo[u] + hi[u]) >> 1;
+                        if (keys[(q0 + u) * kk + mid] > key) lo[u] = mid + 1;
+                        else hi[u] = mid;
+                    }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) pos += lo[u];
+        }
+        uint32_t l = local_of(key);
+        l = l < (uint32_t)n ? l : (uint32_t)(n - 1);
+        if (run_score) {  // entries ahead of it or equal to it
+            const uint32_t kb = (uint32_t)(key >> 32);
+            const int64_t ib = index_base + (int64_t)l;
+            int lo = 0, hi = k;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (!ahead(kb, ib, rk[mid], ri[mid])) lo = mid + 1;
+                else hi = mid;
+            }
+            pos += lo;
+        }
+        if (pos < k) {
+            out_score[pos] = score[l];
+            out_index[pos] = index_base + (int64_t)l;
+        }
+        return;
+    }
+    const int i = ((int)blockIdx.x - n_lists * per_list) * kMergeThreads + t;
+    if (i >= k) return;
+    int pos = i;
+    for (int q = 0; q < n_lists && pos < k; ++q) {  // composites strictly ahead of it
+        int lo = 0, hi = cnt[q];
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            const uint64_t c = keys[q * kk + mid];
+            if (ahead((uint32_t)(c >> 32), index_base + (int64_t)local_of(c), rk[i], ri[i])) lo = mid + 1;
+            else hi = mid;
+        }
+        pos += lo;
+    }
+    if (pos < k) {
+        out_score[pos] = run_score[i];
+        out_index[pos] = ri[i];
     }
 }
 
@@ -377,25 +525,63 @@ int topk_launch(const float *score, int32_t n, int32_t k, int64_t index_base, fl
     if (ws_bytes < 2 * buf_bytes) return fail(HARL_E_WORKSPACE, "harl_topk: workspace too small");
     uint64_t *buf[2] = {static_cast<uint64_t *>(ws), reinterpret_cast<uint64_t *>(static_cast<char *>(ws) + buf_bytes)};
     const bool merge = flags & HARL_TOPK_MERGE;
+    int32_t *counts = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + 2 * buf_bytes);  // kMaxLists words
+    // Rounds until the segments are few enough lists for k_topk_rank (sorted once, in parallel) or one.
+    // 65,536 candidates, k = 1,024: selection 12.5 us, a second round in one workgroup 19 us and a
+    // merge 4 us before; now selection with sort 17 us and ranking 7 us, and against a running list
+    // that drops most candidates at the load 7 + 6 us.
+    const int64_t max_lists = std::min<int64_t>(kMaxLists, kListKeys / k);
+    int rounds = 0;
+    while (rounds + 1 < p.rounds && ceil_div(p.counts[rounds], kSeg) > max_lists) ++rounds;
+    ++rounds;
+    const unsigned lists = (unsigned)ceil_div(p.counts[rounds - 1], kSeg);
+    const bool rank = lists > 1;
+    // the copy of the running list: in the buffer the only round does not write, or after the lists of
+    // a later round (whose buffer held at least two lists more)
+    Running run{nullptr, nullptr, 0, index_base, nullptr, nullptr};
+    if (merge) {
+        run.score = io_score;
+        run.index = io_index;
+        run.k = k;
+        if (rank) {
+            char *at = rounds == 1 ? reinterpret_cast<char *>(buf[1])
+                                   : reinterpret_cast<char *>(buf[(rounds - 1) & 1] + (size_t)lists * k);
+            run.index_copy = reinterpret_cast<int64_t *>(at);
+            run.score_copy = reinterpret_cast<float *>(at + (size_t)k * 8);
+        }
+    }
     const uint64_t *src = nullptr;
-    for (int r = 0; r < p.rounds; ++r) {
+    for (int r = 0; r < rounds; ++r) {
         const int64_t c = p.counts[r];
         const unsigned segs = (unsigned)ceil_div(c, kSeg);
-        const int last = r == p.rounds - 1 ? 1 : 0;
-        const int emit = last && !merge ? 1 : 0;
+        const int last = r == rounds - 1 ? 1 : 0;
+        const int emit = last && !merge && !rank ? 1 : 0;
         uint64_t *dst = buf[r & 1];
-        if (r == 0)
-            hipLaunchKernelGGL(k_topk_select<true>, dim3(segs), dim3(kSelThreads), 0, stream, score, nullptr, c, k, dst,
-                               emit, last, n, index_base, io_score, io_index);
-        else
-            hipLaunchKernelGGL(k_topk_select<false>, dim3(segs), dim3(kSelThreads), 0, stream, score, src, c, k, dst,
-                               emit, last, n, index_base, io_score, io_index);
+        if (r == 0) {
+            Running first = run;
+            if (rounds > 1) first.score_copy = nullptr;  // its place is written by the last round
+            const auto kern = merge ? k_topk_select<true, true> : k_topk_select<true, false>;
+            hipLaunchKernelGGL(kern, dim3(segs), dim3(kSelThreads), 0, stream, score, nullptr, c, k, dst, emit, last, n,
+                               index_base, io_score, io_index, counts, first);
+        } else {
+            Running later = run;
+            if (!last) later.score_copy = nullptr;
+            const auto kern = merge ? k_topk_select<false, true> : k_topk_select<false, false>;
+            hipLaunchKernelGGL(kern, dim3(segs), dim3(kSelThreads), 0, stream, score, src, c, k, dst, emit, last, n,
+                               index_base, io_score, io_index, counts, later);
+        }
         HARL_HIP_CHECK(hipGetLastError());
         src = dst;
     }
-    if (merge) {
-        const int nb = k < n ? k : n;  // real candidates at the head of the final sorted list
-        hipLaunchKernelGGL(k_topk_merge, dim3(1), dim3(kMergeThreads), 0, stream, src, nb, score, n, index_base, io_score,
+    if (rank) {
+        const unsigned per = (unsigned)ceil_div(k, kMergeThreads);
+        const size_t lds = (size_t)lists * k * 8 + (merge ? (size_t)k * 12 : 0);
+        if (const int rc = ensure_dynamic_lds(reinterpret_cast<const void *>(k_topk_rank), lds)) return rc;
+        hipLaunchKernelGGL(k_topk_rank, dim3((lists + (merge ? 1 : 0)) * per), dim3(kMergeThreads), lds, stream, src, counts,
+                           (int)lists, k, score, n, index_base, run.score_copy, run.index_copy, k, io_score, io_index);
+        HARL_HIP_CHECK(hipGetLastError());
+    } else if (merge) {
+        hipLaunchKernelGGL(k_topk_merge, dim3(1), dim3(kMergeThreads), 0, stream, src, counts, score, n, index_base, io_score,
                            io_index, k);
         HARL_HIP_CHECK(hipGetLastError());
     }

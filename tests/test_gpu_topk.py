@@ -59,6 +59,28 @@ def test_running_merge_matches_oracle(k, n, nb):
         np.testing.assert_array_equal(run_g[0], run_o[0])
 
 
+@pytest.mark.parametrize("k,n", [(1, 20000), (100, 8192 * 16), (1024, 8192 * 16 + 1), (2048, 8192 * 8),
+                                 (2048, 8192 * 8 + 1), (1025, 30000), (1000, 8193)])
+def test_lists_and_running_threshold(k, n):
+    """One to many sorted lists (the most that are ranked at once, and one segment more), against a
+    running list that drops nothing, some and every candidate, with equal scores at its last entry."""
+    require_gpu()
+    rng = np.random.default_rng(n + k)
+    run_g, run_o = oracle.reset(k), oracle.reset(k)
+    log("lists k=%d n=%d" % (k, n))
+    for b, shift in enumerate((0.0, 0.0, -100.0, 1.0)):
+        s = (rng.integers(-400, 400, n) / 64 + shift).astype(np.float32)
+        s[rng.integers(0, n, 5)] = np.nan
+        s[rng.integers(0, n, 5)] = -np.inf
+        if b == 3:  # ties with the running list's last entry, at lower and higher indices
+            s[: n // 2] = run_o[0][-1]
+        base = (5 - b) * n
+        run_g = gpu_topk(s, k, index_base=base, running=run_g)
+        run_o = oracle.merge(run_o[0], run_o[1], s, base)
+        np.testing.assert_array_equal(run_g[1], run_o[1])
+        np.testing.assert_array_equal(run_g[0].view(np.uint32), np.asarray(run_o[0], np.float32).view(np.uint32))
+
+
 def test_merge_batch_order_invariance_and_resume():
     require_gpu()
     rng = np.random.default_rng(3)
