@@ -18,8 +18,12 @@
 //    per block, k_elim_scan turns the counts into block offsets, and k_elim_scatter writes each
 //    survivor's index at its position in track order.  No atomics leave a workgroup, so the result
 //    does not depend on scheduling.  Up to kFusedMax tracks, k_elim_fused does all of it in one
-//    workgroup (keys in registers, the histograms in LDS) instead of eleven launches.
+//    workgroup (keys in registers, the histograms in LDS) instead of eleven launches; up to
+//    kChainBlocks blocks, k_elim_pass and k_elim_place do it in five (every workgroup picks the digit
+//    of the pass before by itself, and the per-block counts come from the passes' histograms).
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "internal.hpp"
 
@@ -94,6 +98,28 @@ __global__ __launch_bounds__(kElimThreads) void k_elim_hist(const float *__restr
     hist[(int64_t)blockIdx.x * 256 + t] = h[t];
 }
 
+// The digit d of the need-th largest key of a 256-bin histogram in LDS, and the number of keys with a
+// larger digit; called by the 64 lanes of a wave, one of which returns true and holds both.
+__device__ __forceinline__ bool pick_digit(const uint32_t *h, uint32_t need, uint32_t &d, uint32_t &above) {
+    const int t = threadIdx.x % 64;
+    // lane t holds digits 255-4t .. 252-4t (descending); inclusive prefix over lanes
+    const uint32_t h0 = h[255 - 4 * t], h1 = h[254 - 4 * t], h2 = h[253 - 4 * t], h3 = h[252 - 4 * t];
+    const uint32_t s = h0 + h1 + h2 + h3;
+    uint32_t incl = s;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t v = __shfl_up(incl, o, 64);
+        if (t >= o) incl += v;
+    }
+    above = incl - s;
+    if (above >= need || incl < need) return false;
+    if (above + h0 >= need) d = 255 - 4 * t;
+    else if (above += h0, above + h1 >= need) d = 254 - 4 * t;
+    else if (above += h1, above + h2 >= need) d = 253 - 4 * t;
+    else { above += h2; d = 252 - 4 * t; }
+    return true;
+}
+
 // Sum the block histograms (bins per thread, blocks in order), then pick the digit d of the
 // need-th largest key: the keys with a larger digit number fewer than `need`, those with a digit
 // >= d at least `need`.
@@ -107,27 +133,10 @@ __global__ __launch_bounds__(256) void k_elim_digit(const uint32_t *__restrict__
     const uint32_t need = shift == 24 ? n_keep : st->need;
     const uint32_t prefix = shift == 24 ? 0u : st->prefix;
     __syncthreads();
-    if (t < 64) {
-        // lane t holds digits 255-4t .. 252-4t (descending); inclusive prefix over lanes
-        const uint32_t h0 = h[255 - 4 * t], h1 = h[254 - 4 * t], h2 = h[253 - 4 * t], h3 = h[252 - 4 * t];
-        const uint32_t s = h0 + h1 + h2 + h3;
-        uint32_t incl = s;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t v = __shfl_up(incl, o, 64);
-            if (t >= o) incl += v;
-        }
-        const uint32_t excl = incl - s;
-        if (excl < need && incl >= need) {
-            uint32_t above = excl;
-            int d;
-            if (above + h0 >= need) d = 255 - 4 * t;
-            else if (above += h0, above + h1 >= need) d = 254 - 4 * t;
-            else if (above += h1, above + h2 >= need) d = 253 - 4 * t;
-            else { above += h2; d = 252 - 4 * t; }
-            st->prefix = prefix | ((uint32_t)d << shift);
-            st->need = need - above;
-        }
+    uint32_t d, above;
+    if (t < 64 && pick_digit(h, need, d, above)) {
+        st->prefix = prefix | (d << shift);
+        st->need = need - above;
     }
 }
 
@@ -224,6 +233,145 @@ __global__ __launch_bounds__(kElimThreads) void k_elim_scatter(const float *__re
             eq += key == T;
         }
     }
+}
+
+// ---- K8, sizes between one workgroup and kChainBlocks blocks ----
+// The eleven launches above cost more than their work on such sizes (each kernel reads 16 to 64 blocks'
+// keys or counts and waits for the one before).  Here pass p keeps its histograms in a plane of its
+// own, [blocks][256]; every workgroup of the next kernel sums that plane and picks its digit itself,
+// so no kernel runs between two passes.  A block's keys above T are those that match the digits
+// before some pass and have a larger one in it, which the planes hold, so nothing is counted again.
+// Every workgroup reads blocks KB a pass, which grows with the square of the size: hence the limit
+// (elimination of half the tracks, both sides: 16,385 tracks 48 -> 35 us, 65,536 58 -> 35 us, 262,144
+// 100 -> 45 us).
+constexpr int kChainBlocks = 64;
+
+struct ElimPick {
+    uint32_t prefix, need;
+};
+
+// The digits of T down to that of plane `pass` (shift 24 - 8 pass) and the ranks still needed; state
+// holds what the passes before left (unread for pass 0).  All kElimThreads = 256 threads call.
+__device__ __forceinline__ ElimPick elim_pick(const uint32_t *__restrict__ planes, int n_blocks, int pass, uint32_t n_keep,
+                                              const ElimState *__restrict__ state) {
+    __shared__ uint32_t h[256];
+    __shared__ ElimPick out;
+    const int t = threadIdx.x;
+    const uint32_t *hist = planes + (int64_t)pass * n_blocks * 256;
+    uint32_t c = 0;
+#pragma unroll 8
+    for (int b = 0; b < n_blocks; ++b) c += hist[(int64_t)b * 256 + t];
+    h[t] = c;
+    const uint32_t need = pass == 0 ? n_keep : state[pass].need;
+    const uint32_t prefix = pass == 0 ? 0u : state[pass].prefix;
+    __syncthreads();
+    uint32_t d, above;
+    if (t < 64 && pick_digit(h, need, d, above)) {
+        out.prefix = prefix | (d << (24 - 8 * pass));
+        out.need = need - above;
+    }
+    __syncthreads();
+    return out;
+}
+
+// Pass `pass`: block b's histogram of digit 24 - 8 pass of its keys that match the digits before, into
+// the pass's plane.  Block 0 leaves those digits in state[pass] (a slot per pass: other blocks still
+// read the one before).
+__global__ __launch_bounds__(kElimThreads) void k_elim_pass(const float *__restrict__ adv, int n, int pass, int n_blocks,
+                                                            uint32_t n_keep, ElimState *__restrict__ state,
+                                                            uint32_t *__restrict__ planes) {
+    __shared__ uint32_t h[256];
+    const int t = threadIdx.x, lane = t % 64, shift = 24 - 8 * pass;
+    const int64_t base = (int64_t)blockIdx.x * kElimBlock;
+    uint32_t key[kElimPer];  // loaded ahead of the pick
+#pragma unroll
+    for (int j = 0; j < kElimPer; ++j) {
+        const int64_t i = base + (int64_t)j * kElimThreads + t;
+        key[j] = i < n ? order_key(adv[i]) : 0u;
+    }
+    h[t] = 0;
+    uint32_t prefix = 0;
+    if (pass > 0) {
+        const ElimPick pk = elim_pick(planes, n_blocks, pass - 1, n_keep, state);
+        prefix = pk.prefix;
+        if (blockIdx.x == 0 && t == 0) {
+            state[pass].prefix = pk.prefix;
+            state[pass].need = pk.need;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kElimPer; ++j) {
+        const bool in = base + (int64_t)j * kElimThreads + t < n;
+        const bool alive = in && (pass == 0 || ((key[j] ^ prefix) >> (shift + 8)) == 0);
+        const uint32_t bin = (key[j] >> shift) & 255u;
+        // lanes sharing the first live lane's bin are counted with one atomic
+        const uint64_t live = __ballot(alive);
+        if (live) {
+            const int first = __builtin_ctzll(live);
+            const uint32_t b0 = __builtin_amdgcn_readlane(bin, first);
+            const uint64_t same = __ballot(alive && bin == b0);
+            if (lane == first) atomicAdd(&h[b0], (uint32_t)__popcll(same));
+            if (alive && bin != b0) atomicAdd(&h[bin], 1u);
+        }
+    }
+    __syncthreads();
+    planes[((int64_t)pass * n_blocks + blockIdx.x) * 256 + t] = h[t];
+}
+
+// T from the last plane, the keys above and equal to T in the blocks before this one from all four,
+// and this block's survivors, as in k_elim_scatter.
+__global__ __launch_bounds__(kElimThreads) void k_elim_place(const float *__restrict__ adv, int n, int n_blocks, int n_keep,
+                                                             const ElimState *__restrict__ state,
+                                                             const uint32_t *__restrict__ planes,
+                                                             int32_t *__restrict__ keep_index) {
+    __shared__ uint64_t wsum[kElimThreads / 64], before[kElimThreads / 64];
+    const int t = threadIdx.x;
+    const int64_t i0 = (int64_t)blockIdx.x * kElimBlock + (int64_t)kElimPer * t;
+    uint32_t key[kElimPer];
+#pragma unroll
+    for (int q = 0; q < kElimPer; ++q) key[q] = i0 + q < n ? order_key(adv[i0 + q]) : 0u;
+    const ElimPick pk = elim_pick(planes, n_blocks, 3, (uint32_t)n_keep, state);
+    const uint32_t T = pk.prefix, need = pk.need;
+    // thread t: digit t of the blocks before
+    uint32_t pre_above = 0, pre_eq = 0;
+    for (int p = 0; p < 4; ++p) {
+        const uint32_t dp = (T >> (24 - 8 * p)) & 255u;
+        if ((uint32_t)t < dp || ((uint32_t)t == dp && p < 3)) continue;
+        const uint32_t *hist = planes + (int64_t)p * n_blocks * 256 + t;
+        uint32_t c = 0;
+#pragma unroll 8
+        for (int b = 0; b < (int)blockIdx.x; ++b) c += hist[(int64_t)b * 256];
+        if ((uint32_t)t == dp) pre_eq = c;
+        else pre_above += c;
+    }
+    uint64_t pre = (uint64_t)pre_above | ((uint64_t)pre_eq << 32);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) pre += __shfl_xor(pre, o, 64);
+    if (t % 64 == 0) before[t / 64] = pre;
+    uint32_t above = 0, eq = 0;
+#pragma unroll
+    for (int q = 0; q < kElimPer; ++q)
+        if (i0 + q < n) {
+            above += key[q] > T;
+            eq += key[q] == T;
+        }
+    uint64_t total;
+    // (its barrier also covers `before`)
+    uint64_t ex = block_excl_scan<kElimThreads>((uint64_t)above | ((uint64_t)eq << 32), wsum, total);
+#pragma unroll
+    for (int k = 0; k < kElimThreads / 64; ++k) ex += before[k];
+    above = (uint32_t)ex;
+    eq = (uint32_t)(ex >> 32);
+#pragma unroll
+    for (int q = 0; q < kElimPer; ++q)
+        if (i0 + q < n) {
+            const uint32_t pos = above + (eq < need ? eq : need);
+            const bool keep = key[q] > T || (key[q] == T && eq < need);
+            if (keep && pos < (uint32_t)n_keep) keep_index[pos] = (int32_t)(i0 + q);
+            above += key[q] > T;
+            eq += key[q] == T;
+        }
 }
 
 constexpr int kFusedThreads = 1024, kFusedPer = 16, kFusedMax = kFusedThreads * kFusedPer;
@@ -340,7 +488,9 @@ ElimLayout elim_layout(int32_t n) {
     ElimLayout L{};
     L.state = 0;
     L.hist = 256;
-    L.cnt = L.hist + (size_t)round_up(blocks * 256 * 4, 256);
+    // a plane per pass up to kChainBlocks, one above; never less than for a smaller n
+    const int64_t planes_kb = std::max<int64_t>(4 * std::min<int64_t>(blocks, kChainBlocks), blocks);
+    L.cnt = L.hist + (size_t)planes_kb * 1024;
     L.off = L.cnt + (size_t)round_up(blocks * 8, 256);
     L.total = L.off + (size_t)round_up(blocks * 8, 256);
     return L;
@@ -396,6 +546,18 @@ int track_eliminate_launch(const float *adv, int32_t n, int32_t n_keep, int32_t 
         uint32_t *hist = reinterpret_cast<uint32_t *>(w + L.hist);
         uint64_t *cnt = reinterpret_cast<uint64_t *>(w + L.cnt), *off = reinterpret_cast<uint64_t *>(w + L.off);
         const int blocks = (int)ceil_div(n, kElimBlock);
+        if (blocks <= kChainBlocks) {
+            for (int pass = 0; pass < 4; ++pass) {
+                hipLaunchKernelGGL(k_elim_pass, dim3(blocks), dim3(kElimThreads), 0, stream, adv, n, pass, blocks,
+                                   (uint32_t)n_keep, st, hist);
+                HARL_HIP_CHECK(hipGetLastError());
+            }
+            hipLaunchKernelGGL(k_elim_place, dim3(blocks), dim3(kElimThreads), 0, stream, adv, n, blocks, n_keep, st, hist,
+                               keep_index);
+            HARL_HIP_CHECK(hipGetLastError());
+            if (rows_out) return gather_launch(rows, row_bytes, keep_index, n_keep, rows_out, stream);
+            return HARL_OK;
+        }
         for (int shift = 24; shift >= 0; shift -= 8) {
             hipLaunchKernelGGL(k_elim_hist, dim3(blocks), dim3(kElimThreads), 0, stream, adv, n, shift, st, hist);
             HARL_HIP_CHECK(hipGetLastError());

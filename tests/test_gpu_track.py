@@ -128,6 +128,25 @@ def test_eliminate_all_equal_and_large():
     np.testing.assert_array_equal(got, oracle.track_eliminate(adv, n_keep))
 
 
+@pytest.mark.parametrize("n", [16385, 20480, 20481, 258048, 262143, 262144, 262145])
+@pytest.mark.parametrize("kind", ["normal", "few values", "infinities and NaN"])
+def test_eliminate_around_the_launch_chains(n, kind):
+    """Sizes around one workgroup's limit (16,384), block edges (4,096) and the largest size that picks
+    its digits inside the passes (64 blocks), from a workspace of leftover bytes; exact."""
+    require_gpu()
+    rng = np.random.default_rng(n)
+    adv = rng.standard_normal(n).astype(np.float32)
+    if kind == "few values":
+        adv = rng.choice(np.array([-1.0, -0.0, 0.0, 1.0, 1.0000001], np.float32), n)
+    elif kind == "infinities and NaN":
+        adv[rng.random(n) < 0.3] = np.inf
+        adv[rng.random(n) < 0.3] = -np.inf
+        adv[rng.random(n) < 0.3] = np.nan
+    for n_keep in (1, n // 2, n - 1):
+        got, _ = gpu_eliminate(adv, n_keep, ws_fill=0xFF)
+        np.testing.assert_array_equal(got, oracle.track_eliminate(adv, n_keep))
+
+
 @pytest.mark.parametrize("dtype,width", [(np.float32, 64), (np.uint16, 128), (np.uint8, 7), (np.float32, 3)])
 def test_eliminate_gathers_rows(dtype, width):
     require_gpu()
