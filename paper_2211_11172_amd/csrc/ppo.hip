@@ -19,10 +19,11 @@
 //              the batch in fixed-order split-K pieces summed in order
 //   Adam       bias-corrected, the actor's rate for the trunk and actor head, the critic's for the
 //              value head (k_adam)
-// k_gemm: C[i][j] = sum_p A(i, p) B(p, j) with A(i, p) = A[i a_si + p a_sp], B(p, j) = B[p b_sp +
-// j b_sj] (any transpose), fp32 on v_mfma_f32_16x16x4f32: a workgroup of 4 waves owns a 64 x 64
-// tile of C (a wave 32 x 32, 2 x 2 MFMA tiles; 32 x 64 when the grid would be small), K is staged through LDS 32 at a time while the next
-// 32 are loaded into registers.  No result depends on scheduling.
+// k_gemm_v, k_gemm: C[i][j] = sum_p A(i, p) B(p, j) with A(i, p) = A[i a_si + p a_sp], B(p, j) =
+// B[p b_sp + j b_sj] (any transpose), fp32 on v_mfma_f32_16x16x4f32 by workgroups of 4 waves; K is
+// staged through LDS, the next stage loaded into registers while one runs.  k_gemm takes operands
+// whose sizes or alignment rule out 16-byte loads, k_gemm_v all others.  No result depends on
+// scheduling.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -42,7 +43,7 @@ constexpr int kLossChunk = 4096;  // rows per loss partial (large batches)
 enum Epilogue : int { kPlain = 0, kBias = 1, kBiasRelu = 2, kReluMask = 3 };
 
 struct GemmArgs {
-    const float *A;  // null: A(i, p) = 1 (column sums)
+    const float *A;
     int64_t a_si, a_sp;
     const float *B;
     int64_t b_sp, b_sj;
@@ -59,68 +60,70 @@ struct GemmArgs {
     float *last_out;              //   row rows_w, if last_out, to last_out[j]; later rows nowhere
 };
 
+// A wave's tiles of C at (i0, j0) through the epilogue: accumulator register r of tile (x, y) is
+// C[i0 + 16x + 4(l/16) + r][j0 + 16y + l%16].
+template <int XT, int YT>
+__device__ __forceinline__ void store_tile(const GemmArgs &g, const f32x4 (&acc)[XT][YT], int i0, int j0, int piece) {
+    const int l = threadIdx.x % 64;
+#pragma unroll
+    for (int x = 0; x < XT; ++x)
+#pragma unroll
+        for (int y = 0; y < YT; ++y)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int i = i0 + 16 * x + 4 * (l / 16) + r, j = j0 + 16 * y + l % 16;
+                if (i >= g.I || j >= g.J - g.ones) continue;
+                float v = acc[x][y][r];
+                if (g.split) {
+                    g.C[((int64_t)piece * g.I + i) * g.J + j] = v;
+                    continue;
+                }
+                if (g.epi == kBias || g.epi == kBiasRelu) v += g.bias[j];
+                if (g.epi == kBiasRelu) v = fmaxf(v, 0.f);
+                if (g.epi == kReluMask) v = g.mask[(int64_t)i * g.ldm + j] > 0.f ? v : 0.f;
+                g.C[(int64_t)i * g.ldc + j] = v;
+            }
+}
+
 // Operand elements of the K step starting at p0 for this thread: A's TI x TK and B's TK x 64
-// tiles, the tile index moving fastest along the operand's contiguous direction.  VEC: 16-byte
-// loads of 4 elements consecutive along that direction (the host checks that every such group is
-// wholly inside or wholly outside the operand and 16-byte aligned); otherwise one element per load.
-template <int TI, int TK, bool VEC>
+// tiles, the tile index moving fastest along the operand's contiguous direction, an element per load
+// (operands that 16-byte loads cannot take; k_gemm_v has the others).
+template <int TI, int TK>
 struct Frag {
-    static constexpr int W = VEC ? 4 : 1;
-    static constexpr int NA = TI * TK / (kGemmThreads * W), NB = kTile * TK / (kGemmThreads * W);
-    float a[NA][W], b[NB][W];
+    static constexpr int NA = TI * TK / kGemmThreads, NB = kTile * TK / kGemmThreads;
+    float a[NA], b[NB];
 };
 
-template <int TI, int TK, bool VEC>
-__device__ __forceinline__ void gemm_fetch(const GemmArgs &g, int i0, int j0, int p0, int p_end, Frag<TI, TK, VEC> &f) {
-    using F = Frag<TI, TK, VEC>;
-    constexpr int W = F::W;
+template <int TI, int TK>
+__device__ __forceinline__ void gemm_fetch(const GemmArgs &g, int i0, int j0, int p0, int p_end, Frag<TI, TK> &f) {
+    using F = Frag<TI, TK>;
     const int t = threadIdx.x;
     const bool a_i_fast = g.a_si == 1, b_p_fast = g.b_sp == 1;
 #pragma unroll
     for (int q = 0; q < F::NA; ++q) {
         const int e = t + kGemmThreads * q;
-        // element (ii, pp) is the first of the group
-        const int ii = a_i_fast ? (e % (TI / W)) * W : e / (TK / W), pp = a_i_fast ? e / (TI / W) : (e % (TK / W)) * W;
+        const int ii = a_i_fast ? e % TI : e / TK, pp = a_i_fast ? e / TI : e % TK;
         const int gi = i0 + ii, gp = p0 + pp;
-        if constexpr (VEC) {
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (gi < g.I && gp < p_end) v = *reinterpret_cast<const float4 *>(g.A + (int64_t)gi * g.a_si + (int64_t)gp * g.a_sp);
-            f.a[q][0] = v.x;
-            f.a[q][1] = v.y;
-            f.a[q][2] = v.z;
-            f.a[q][3] = v.w;
-        } else {
-            float v = 0.f;
-            if (gi < g.I && gp < p_end) v = g.A ? g.A[(int64_t)gi * g.a_si + (int64_t)gp * g.a_sp] : 1.f;
-            f.a[q][0] = v;
-        }
+        float v = 0.f;
+        if (gi < g.I && gp < p_end) v = g.A[(int64_t)gi * g.a_si + (int64_t)gp * g.a_sp];
+        f.a[q] = v;
     }
 #pragma unroll
     for (int q = 0; q < F::NB; ++q) {
         const int e = t + kGemmThreads * q;
-        const int pb = b_p_fast ? (e % (TK / W)) * W : e / (kTile / W), jb = b_p_fast ? e / (TK / W) : (e % (kTile / W)) * W;
+        const int pb = b_p_fast ? e % TK : e / kTile, jb = b_p_fast ? e / TK : e % kTile;
         const int gpb = p0 + pb, gj = j0 + jb;
         const int J0 = g.J - g.ones;  // B's columns
-        if constexpr (VEC) {
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (gpb < p_end && gj < J0)
-                v = *reinterpret_cast<const float4 *>(g.B + (int64_t)gpb * g.b_sp + (int64_t)gj * g.b_sj);
-            f.b[q][0] = v.x;
-            f.b[q][1] = v.y;
-            f.b[q][2] = v.z;
-            f.b[q][3] = v.w;
-        } else {
-            f.b[q][0] = (gpb < p_end && gj < J0) ? g.B[(int64_t)gpb * g.b_sp + (int64_t)gj * g.b_sj] : 0.f;
-        }
+        f.b[q] = (gpb < p_end && gj < J0) ? g.B[(int64_t)gpb * g.b_sp + (int64_t)gj * g.b_sj] : 0.f;
     }
 }
 
 // TI rows (64 or 32) by 64 columns of C per workgroup; wave w owns rows (w / 2) TI / 2 .. and
 // columns (w % 2) 32 ..
-template <int TI, int TK, bool VEC>
+template <int TI, int TK>
 __global__ __launch_bounds__(kGemmThreads) void k_gemm(GemmArgs g) {
-    using F = Frag<TI, TK, VEC>;
-    constexpr int XT = TI / 32, W = F::W;
+    using F = Frag<TI, TK>;
+    constexpr int XT = TI / 32;
     __shared__ float As[TI][TK + 1];
     __shared__ float Bs[TK][kTile + 1];
     const int t = threadIdx.x, wv = t / 64, l = t % 64;
@@ -138,25 +141,23 @@ __global__ __launch_bounds__(kGemmThreads) void k_gemm(GemmArgs g) {
     // the column-0 workgroups of a GEMM with g.ones also sum A's rows: thread t < TI, row t
     const bool rowsum = g.ones && blockIdx.x == 0 && t < TI;
     float rs = 0.f;
-    if (p_begin < p_end) gemm_fetch<TI, TK, VEC>(g, i0, j0, p_begin, p_end, fr);
+    if (p_begin < p_end) gemm_fetch<TI, TK>(g, i0, j0, p_begin, p_end, fr);
     for (int p0 = p_begin; p0 < p_end; p0 += TK) {
 #pragma unroll
         for (int q = 0; q < F::NA; ++q) {
             const int e = t + kGemmThreads * q;
-            const int ii = a_i_fast ? (e % (TI / W)) * W : e / (TK / W), pp = a_i_fast ? e / (TI / W) : (e % (TK / W)) * W;
-#pragma unroll
-            for (int u = 0; u < W; ++u) As[ii + (a_i_fast ? u : 0)][pp + (a_i_fast ? 0 : u)] = fr.a[q][u];
+            const int ii = a_i_fast ? e % TI : e / TK, pp = a_i_fast ? e / TI : e % TK;
+            As[ii][pp] = fr.a[q];
         }
 #pragma unroll
         for (int q = 0; q < F::NB; ++q) {
             const int e = t + kGemmThreads * q;
-            const int pb = b_p_fast ? (e % (TK / W)) * W : e / (kTile / W), jb = b_p_fast ? e / (TK / W) : (e % (kTile / W)) * W;
-#pragma unroll
-            for (int u = 0; u < W; ++u) Bs[pb + (b_p_fast ? u : 0)][jb + (b_p_fast ? 0 : u)] = fr.b[q][u];
+            const int pb = b_p_fast ? e % TK : e / kTile, jb = b_p_fast ? e / TK : e % kTile;
+            Bs[pb][jb] = fr.b[q];
         }
         __syncthreads();
         // the next K step's operands are loaded while this one runs on the matrix cores
-        if (p0 + TK < p_end) gemm_fetch<TI, TK, VEC>(g, i0, j0, p0 + TK, p_end, fr);
+        if (p0 + TK < p_end) gemm_fetch<TI, TK>(g, i0, j0, p0 + TK, p_end, fr);
         if (rowsum)
 #pragma unroll 8
             for (int kk = 0; kk < TK; ++kk) rs += As[t][kk];  // in p order; staged zeros past p_end
@@ -179,25 +180,132 @@ __global__ __launch_bounds__(kGemmThreads) void k_gemm(GemmArgs g) {
         if (g.split) g.C[((int64_t)blockIdx.z * g.I + i) * g.J + g.J - 1] = rs;
         else g.C[(int64_t)i * g.ldc + g.J - 1] = rs;
     }
-    // accumulator register r of tile (x, y) is C[wi + 16x + 4(l/16) + r][wj + 16y + l%16]
+    store_tile<XT, 2>(g, acc, i0 + wi, j0 + wj, blockIdx.z);
+}
+
+// GEMMs whose operands take 16-byte loads.  A workgroup owns a TI x TJ tile of C (4 waves, 2 x 2, each
+// TI / 2 x TJ / 2); both operands are staged K-contiguous, [row][TK + 4], whichever way they lie in
+// memory, so that a lane reads the four K values of four MFMAs with one 16-byte LDS read: lane group q
+// = l / 16 holds k = 16 c + 4 q + u for MFMA u of chunk c, the same for A and B, and a wave needs
+// (TI + TJ) / 32 reads for TI TJ / 256 MFMAs.  The row stride of TK + 4 floats spreads 16 rows' reads
+// over all banks.  An operand that is contiguous along its rows is loaded 8 K values x 8 groups of
+// rows (128-byte lines) per wave and transposed by four 4-byte LDS stores per lane.  Before, every
+// MFMA took two 4-byte LDS reads, row tiles were 64 at most, heads of 27 columns took 64, and tiles
+// that share an operand lay on different XCDs: an update of 65,536 transitions took 595 us, now 512;
+// of 4,096 transitions 99.5 us, now 95.8.
+template <int T, int TK>
+__device__ __forceinline__ void stage_at(bool row_fast, int e, int &row, int &k) {
+    if (row_fast) {
+        k = e % 8 + 8 * (e / (8 * (T / 4)));
+        row = (e / 8) % (T / 4) * 4;
+    } else {
+        k = e % (TK / 4) * 4;
+        row = e / (TK / 4);
+    }
+}
+
+// Rows [r0, r0 + T) below `rows` and K values [p0, p0 + TK) below p_end of an operand; zeros outside.
+template <int T, int TK>
+__device__ __forceinline__ void stage_load(const float *__restrict__ X, int64_t s_row, int64_t s_p, int r0, int rows, int p0,
+                                           int p_end, float4 (&v)[T * TK / 1024]) {
+    const bool row_fast = s_row == 1;
+#pragma unroll
+    for (int q = 0; q < T * TK / 1024; ++q) {
+        int row, k;
+        stage_at<T, TK>(row_fast, threadIdx.x + kGemmThreads * q, row, k);
+        v[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (r0 + row < rows && p0 + k < p_end)
+            v[q] = *reinterpret_cast<const float4 *>(X + (int64_t)(r0 + row) * s_row + (int64_t)(p0 + k) * s_p);
+    }
+}
+
+template <int T, int TK>
+__device__ __forceinline__ void stage_store(bool row_fast, const float4 (&v)[T * TK / 1024], float (*S)[TK + 4]) {
+#pragma unroll
+    for (int q = 0; q < T * TK / 1024; ++q) {
+        int row, k;
+        stage_at<T, TK>(row_fast, threadIdx.x + kGemmThreads * q, row, k);
+        if (row_fast) {
+            S[row][k] = v[q].x;
+            S[row + 1][k] = v[q].y;
+            S[row + 2][k] = v[q].z;
+            S[row + 3][k] = v[q].w;
+        } else {
+            *reinterpret_cast<float4 *>(&S[row][k]) = v[q];
+        }
+    }
+}
+
+// The grid is one-dimensional: workgroups w, w + 8, ... (one XCD) take all tiles that share an operand
+// (the column tiles of a row tile; with split K all tiles of a piece) one after another, so that the
+// shared operand is read into one L2.  Workgroups past the last group leave at once.
+template <int TI, int TJ, int TK>
+__global__ __launch_bounds__(kGemmThreads) void k_gemm_v(GemmArgs g, int gx, int gy, int pieces) {
+    constexpr int XT = TI / 32, YT = TJ / 32;
+    __shared__ __attribute__((aligned(16))) float As[TI][TK + 4];
+    __shared__ __attribute__((aligned(16))) float Bs[TJ][TK + 4];
+    const int t = threadIdx.x, wv = t / 64, l = t % 64;
+    const int minor_n = g.split ? gx * gy : gx, s = blockIdx.x / 8;
+    const int minor = s % minor_n, major = s / minor_n * 8 + blockIdx.x % 8;
+    if (major >= (g.split ? pieces : gy)) return;
+    const int bx = minor % gx, by = g.split ? minor / gx : major, bz = g.split ? major : 0;
+    const int i0 = by * TI, j0 = bx * TJ, J0 = g.J - g.ones;
+    const int p_begin = bz * g.p_per_split;
+    const int p_end = g.P - p_begin < g.p_per_split ? g.P : p_begin + g.p_per_split;
+    const int wi = (wv / 2) * (16 * XT), wj = (wv % 2) * (16 * YT);
+    const bool a_fast = g.a_si == 1, b_fast = g.b_sj == 1;
+    f32x4 acc[XT][YT];
 #pragma unroll
     for (int x = 0; x < XT; ++x)
 #pragma unroll
-        for (int y = 0; y < 2; ++y)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int i = i0 + wi + 16 * x + 4 * (l / 16) + r, j = j0 + wj + 16 * y + l % 16;
-                if (i >= g.I || j >= g.J - g.ones) continue;
-                float v = acc[x][y][r];
-                if (g.split) {
-                    g.C[((int64_t)blockIdx.z * g.I + i) * g.J + j] = v;
-                    continue;
-                }
-                if (g.epi == kBias || g.epi == kBiasRelu) v += g.bias[j];
-                if (g.epi == kBiasRelu) v = fmaxf(v, 0.f);
-                if (g.epi == kReluMask) v = g.mask[(int64_t)i * g.ldm + j] > 0.f ? v : 0.f;
-                g.C[(int64_t)i * g.ldc + j] = v;
+        for (int y = 0; y < YT; ++y) acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // the column-0 workgroups of a GEMM with g.ones also sum A's rows: thread t < TI, row t
+    const bool rowsum = g.ones && bx == 0 && t < TI;
+    float rs = 0.f;
+    float4 fa[TI * TK / 1024], fb[TJ * TK / 1024];
+    stage_load<TI, TK>(g.A, g.a_si, g.a_sp, i0, g.I, p_begin, p_end, fa);
+    stage_load<TJ, TK>(g.B, g.b_sj, g.b_sp, j0, J0, p_begin, p_end, fb);
+    for (int p0 = p_begin; p0 < p_end; p0 += TK) {
+        stage_store<TI, TK>(a_fast, fa, As);
+        stage_store<TJ, TK>(b_fast, fb, Bs);
+        __syncthreads();
+        // the next K step's operands are loaded while this one runs on the matrix cores
+        if (p0 + TK < p_end) {
+            stage_load<TI, TK>(g.A, g.a_si, g.a_sp, i0, g.I, p0 + TK, p_end, fa);
+            stage_load<TJ, TK>(g.B, g.b_sj, g.b_sp, j0, J0, p0 + TK, p_end, fb);
+        }
+        if (rowsum)
+#pragma unroll 4
+            for (int kk = 0; kk < TK; kk += 4) {  // in p order; staged zeros past p_end
+                const float4 v = *reinterpret_cast<const float4 *>(&As[t][kk]);
+                rs += v.x;
+                rs += v.y;
+                rs += v.z;
+                rs += v.w;
             }
+#pragma unroll
+        for (int kk = 0; kk < TK; kk += 16) {
+            f32x4 a[XT], b[YT];
+#pragma unroll
+            for (int x = 0; x < XT; ++x) a[x] = *reinterpret_cast<const f32x4 *>(&As[wi + 16 * x + l % 16][kk + 4 * (l / 16)]);
+#pragma unroll
+            for (int y = 0; y < YT; ++y) b[y] = *reinterpret_cast<const f32x4 *>(&Bs[wj + 16 * y + l % 16][kk + 4 * (l / 16)]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int x = 0; x < XT; ++x)
+#pragma unroll
+                    for (int y = 0; y < YT; ++y)
+                        acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[x][u], b[y][u], acc[x][y], 0, 0, 0);
+        }
+        __syncthreads();
+    }
+    if (rowsum && i0 + t < g.I) {
+        const int i = i0 + t;
+        if (g.split) g.C[((int64_t)bz * g.I + i) * g.J + g.J - 1] = rs;
+        else g.C[(int64_t)i * g.ldc + g.J - 1] = rs;
+    }
+    store_tile<XT, YT>(g, acc, i0 + wi, j0 + wj, bz);
 }
 
 // The sum over splits (in order) of partial[s][e], e < n = I J, row r = e / J, column c = e % J:
@@ -495,33 +603,28 @@ Ws ws_layout(const harl_ppo_config *c, int32_t M, char *base) {
 // 16-byte operand loads are safe when each operand's contiguous dimension and other stride are
 // multiples of 4 and its base is 16-byte aligned (then a group of 4 is wholly in or out of range).
 bool vec_ok(const GemmArgs &g) {
-    if (!g.A || !aligned(g.A, 16) || !aligned(g.B, 16)) return false;
+    if (!aligned(g.A, 16) || !aligned(g.B, 16)) return false;
     const bool a_ok = g.a_si == 1 ? (g.I % 4 == 0 && g.a_sp % 4 == 0) : (g.a_sp == 1 && g.P % 4 == 0 && g.a_si % 4 == 0);
     const int J0 = g.J - g.ones;  // B's columns
     const bool b_ok = g.b_sp == 1 ? (g.P % 4 == 0 && g.b_sj % 4 == 0) : (g.b_sj == 1 && J0 % 4 == 0 && g.b_sp % 4 == 0);
     return a_ok && b_ok;
 }
 
-template <int TK, bool VEC>
-void launch_gemm(const GemmArgs &g, unsigned gx, int used, hipStream_t stream) {
-    // 32-row tiles when 64-row tiles would leave the machine short of workgroups
-    const bool small = (int64_t)gx * ceil_div(g.I, 64) * used < 1024 && g.I > 32;
-    if (small)
-        hipLaunchKernelGGL((k_gemm<32, TK, VEC>), dim3(gx, (unsigned)ceil_div(g.I, 32), used), dim3(kGemmThreads), 0,
-                           stream, g);
-    else
-        hipLaunchKernelGGL((k_gemm<64, TK, VEC>), dim3(gx, (unsigned)ceil_div(g.I, 64), used), dim3(kGemmThreads), 0,
-                           stream, g);
+template <int TI, int TJ, int TK>
+void launch_gemm_v(const GemmArgs &g, int pieces, hipStream_t stream) {
+    const int64_t gx = ceil_div(g.J - g.ones, TJ), gy = ceil_div(g.I, TI);
+    const int64_t grid = g.split ? round_up(pieces, 8) * gx * gy : round_up(gy, 8) * gx;
+    hipLaunchKernelGGL((k_gemm_v<TI, TJ, TK>), dim3((unsigned)grid), dim3(kGemmThreads), 0, stream, g, (int)gx, (int)gy, pieces);
 }
 
 int gemm(const GemmArgs &g0, float *partial, hipStream_t stream) {
     GemmArgs g = g0;
-    const unsigned gx = (unsigned)ceil_div(g.J - g.ones, kTile);
+    const int J0 = g.J - g.ones;
     const bool vec = vec_ok(g);
-    const int tk = vec ? 2 * kTileK : kTileK;  // 64-deep K stages with 16-byte loads, else 32
+    const int tk = vec ? 2 * kTileK : kTileK;
     int used = 1;
     if (g.split) {
-        const int splits = splits_for(g.P, g.I, g.J - g.ones);
+        const int splits = splits_for(g.P, g.I, J0);
         g.p_per_split = (int)round_up(ceil_div(g.P, splits), tk);
         used = (int)ceil_div(g.P, g.p_per_split);
     } else {
@@ -529,10 +632,28 @@ int gemm(const GemmArgs &g0, float *partial, hipStream_t stream) {
     }
     float *out = g.C;
     if (g.split) g.C = partial;
-    if (vec)
-        launch_gemm<2 * kTileK, true>(g, gx, used, stream);
-    else
-        launch_gemm<kTileK, false>(g, gx, used, stream);
+    // the largest tile that leaves the machine at least four workgroups per CU (what its registers
+    // let a CU hold); tiles of 32 also where C has no more rows or columns (the head's product of
+    // 65,536 rows and 26 columns: 30 us on tiles of 64 columns, 19.5 on 32)
+    auto fills = [&](int ti, int tj) { return ceil_div(J0, tj) * ceil_div(g.I, ti) * used >= 1024; };
+    if (vec) {
+        if (J0 <= 32) {
+            if (fills(64, 32)) launch_gemm_v<64, 32, 64>(g, used, stream);
+            else launch_gemm_v<32, 32, 64>(g, used, stream);
+        } else if (fills(128, 64)) {
+            launch_gemm_v<128, 64, 32>(g, used, stream);
+        } else if (fills(64, 64) && g.I > 32) {
+            launch_gemm_v<64, 64, 64>(g, used, stream);
+        } else {
+            launch_gemm_v<32, 64, 64>(g, used, stream);
+        }
+    } else if (fills(64, kTile) || g.I <= 32) {
+        hipLaunchKernelGGL((k_gemm<64, kTileK>), dim3((unsigned)ceil_div(J0, kTile), (unsigned)ceil_div(g.I, 64), used),
+                           dim3(kGemmThreads), 0, stream, g);
+    } else {
+        hipLaunchKernelGGL((k_gemm<32, kTileK>), dim3((unsigned)ceil_div(J0, kTile), (unsigned)ceil_div(g.I, 32), used),
+                           dim3(kGemmThreads), 0, stream, g);
+    }
     HARL_HIP_CHECK(hipGetLastError());
     if (g.split) {
         const int64_t n = (int64_t)g.I * g.J;  // out is contiguous [I][J]

@@ -116,6 +116,18 @@ def test_ppo_update_odd_shapes_and_segments():
     _check_step(flat, np.zeros(flat.size), np.zeros(flat.size), 1, batch, out[0], dims, segs)
 
 
+# row tiles of 128, 64 and 32 with a ragged last one, column tiles of 64 and 32, K not a multiple of a
+# stage, rows that no multiple of 4 divides (the transposed operands), a head of one tile and of two
+@pytest.mark.parametrize("M,dims", [(43661, (36, 132, 196, 30)), (16385, (4, 68, 260, 31)), (4097, (8, 36, 100, 33)),
+                                    (127, (64, 256, 256, 26))])
+def test_ppo_update_tile_edges(M, dims):
+    require_gpu()
+    segs = [0, 3, dims[3] - 4, dims[3]]
+    flat, batch = _setup(M, dims, segs, seed=M)
+    out = _gpu_update(flat, batch, dims, segs, steps=1)
+    _check_step(flat, np.zeros(flat.size), np.zeros(flat.size), 1, batch, out[0], dims, segs)
+
+
 def test_ppo_update_is_deterministic():
     require_gpu()
     dims = (64, 256, 256, 26)
