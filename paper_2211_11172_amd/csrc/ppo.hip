@@ -85,6 +85,37 @@ __device__ __forceinline__ void store_tile(const GemmArgs &g, const f32x4 (&acc)
             }
 }
 
+// The same for tiles computed as C^T (MFMA operands swapped): register r of tile (x, y) is C[i0 + 16x +
+// l%16][j0 + 16y + 4(l/16) + r], so that a lane's four results, its bias and its mask are 16 bytes each
+// (64 -> 256 columns at 65,536 rows: 41.9 -> 33.5 us, 256 -> 256: 103 -> 92 us; an update 512 -> 480 us).
+template <int XT, int YT>
+__device__ __forceinline__ void store_tile_t(const GemmArgs &g, const f32x4 (&acc)[XT][YT], int i0, int j0) {
+    const int l = threadIdx.x % 64;
+#pragma unroll
+    for (int y = 0; y < YT; ++y) {
+        const int j = j0 + 16 * y + 4 * (l / 16);
+        if (j >= g.J) continue;
+        f32x4 bias = {0.f, 0.f, 0.f, 0.f};
+        if (g.epi == kBias || g.epi == kBiasRelu) bias = *reinterpret_cast<const f32x4 *>(g.bias + j);
+#pragma unroll
+        for (int x = 0; x < XT; ++x) {
+            const int i = i0 + 16 * x + l % 16;
+            if (i >= g.I) continue;
+            f32x4 v = acc[x][y];
+            if (g.epi == kBias || g.epi == kBiasRelu) v += bias;
+            if (g.epi == kBiasRelu)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], 0.f);
+            if (g.epi == kReluMask) {
+                const f32x4 m = *reinterpret_cast<const f32x4 *>(g.mask + (int64_t)i * g.ldm + j);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] = m[r] > 0.f ? v[r] : 0.f;
+            }
+            *reinterpret_cast<f32x4 *>(g.C + (int64_t)i * g.ldc + j) = v;
+        }
+    }
+}
+
 // Operand elements of the K step starting at p0 for this thread: A's TI x TK and B's TK x 64
 // tiles, the tile index moving fastest along the operand's contiguous direction, an element per load
 // (operands that 16-byte loads cannot take; k_gemm_v has the others).
@@ -191,8 +222,8 @@ __global__ __launch_bounds__(kGemmThreads) void k_gemm(GemmArgs g) {
 // over all banks.  An operand that is contiguous along its rows is loaded 8 K values x 8 groups of
 // rows (128-byte lines) per wave and transposed by four 4-byte LDS stores per lane.  Before, every
 // MFMA took two 4-byte LDS reads, row tiles were 64 at most, heads of 27 columns took 64, and tiles
-// that share an operand lay on different XCDs: an update of 65,536 transitions took 595 us, now 512;
-// of 4,096 transitions 99.5 us, now 95.8.
+// that share an operand lay on different XCDs: an update of 65,536 transitions took 595 us and then
+// 512, of 4,096 transitions 99.5 us and then 95.8.
 template <int T, int TK>
 __device__ __forceinline__ void stage_at(bool row_fast, int e, int &row, int &k) {
     if (row_fast) {
@@ -239,7 +270,7 @@ __device__ __forceinline__ void stage_store(bool row_fast, const float4 (&v)[T *
 // The grid is one-dimensional: workgroups w, w + 8, ... (one XCD) take all tiles that share an operand
 // (the column tiles of a row tile; with split K all tiles of a piece) one after another, so that the
 // shared operand is read into one L2.  Workgroups past the last group leave at once.
-template <int TI, int TJ, int TK>
+template <int TI, int TJ, int TK, bool VST>
 __global__ __launch_bounds__(kGemmThreads) void k_gemm_v(GemmArgs g, int gx, int gy, int pieces) {
     constexpr int XT = TI / 32, YT = TJ / 32;
     __shared__ __attribute__((aligned(16))) float As[TI][TK + 4];
@@ -296,7 +327,8 @@ __global__ __launch_bounds__(kGemmThreads) void k_gemm_v(GemmArgs g, int gx, int
                 for (int x = 0; x < XT; ++x)
 #pragma unroll
                     for (int y = 0; y < YT; ++y)
-                        acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[x][u], b[y][u], acc[x][y], 0, 0, 0);
+                        acc[x][y] = VST ? __builtin_amdgcn_mfma_f32_16x16x4f32(b[y][u], a[x][u], acc[x][y], 0, 0, 0)
+                                        : __builtin_amdgcn_mfma_f32_16x16x4f32(a[x][u], b[y][u], acc[x][y], 0, 0, 0);
         }
         __syncthreads();
     }
@@ -305,7 +337,8 @@ __global__ __launch_bounds__(kGemmThreads) void k_gemm_v(GemmArgs g, int gx, int
         if (g.split) g.C[((int64_t)bz * g.I + i) * g.J + g.J - 1] = rs;
         else g.C[(int64_t)i * g.ldc + g.J - 1] = rs;
     }
-    store_tile<XT, YT>(g, acc, i0 + wi, j0 + wj, bz);
+    if constexpr (VST) store_tile_t<XT, YT>(g, acc, i0 + wi, j0 + wj);
+    else store_tile<XT, YT>(g, acc, i0 + wi, j0 + wj, bz);
 }
 
 // The sum over splits (in order) of partial[s][e], e < n = I J, row r = e / J, column c = e % J:
@@ -610,11 +643,24 @@ bool vec_ok(const GemmArgs &g) {
     return a_ok && b_ok;
 }
 
+// Results, bias and mask go 16 bytes at a time when every group of 4 columns is wholly inside C and
+// aligned; pieces of a split product (rows of J0 + 1) and heads of other widths go one by one.
+bool vec_store_ok(const GemmArgs &g) {
+    if (g.split || g.ones || g.J % 4 || g.ldc % 4 || !aligned(g.C, 16)) return false;
+    if ((g.epi == kBias || g.epi == kBiasRelu) && !aligned(g.bias, 16)) return false;
+    return g.epi != kReluMask || (g.ldm % 4 == 0 && aligned(g.mask, 16));
+}
+
 template <int TI, int TJ, int TK>
 void launch_gemm_v(const GemmArgs &g, int pieces, hipStream_t stream) {
     const int64_t gx = ceil_div(g.J - g.ones, TJ), gy = ceil_div(g.I, TI);
     const int64_t grid = g.split ? round_up(pieces, 8) * gx * gy : round_up(gy, 8) * gx;
-    hipLaunchKernelGGL((k_gemm_v<TI, TJ, TK>), dim3((unsigned)grid), dim3(kGemmThreads), 0, stream, g, (int)gx, (int)gy, pieces);
+    if (vec_store_ok(g))
+        hipLaunchKernelGGL((k_gemm_v<TI, TJ, TK, true>), dim3((unsigned)grid), dim3(kGemmThreads), 0, stream, g, (int)gx,
+                           (int)gy, pieces);
+    else
+        hipLaunchKernelGGL((k_gemm_v<TI, TJ, TK, false>), dim3((unsigned)grid), dim3(kGemmThreads), 0, stream, g, (int)gx,
+                           (int)gy, pieces);
 }
 
 int gemm(const GemmArgs &g0, float *partial, hipStream_t stream) {
