@@ -772,8 +772,10 @@ __global__ __launch_bounds__(kThreads, 3) void k_gb_hist(HistArgs a, Ws w) {
                 }
             }
         };
-        rows_at(i0);
-        load(word, q);
+        if (i0 < i1) {  // a node without rows loads nothing: with no rows at all the bins may be null
+            rows_at(i0);
+            load(word, q);
+        }
         for (int b0 = i0; b0 < i1; b0 += (4 * kThreads)) {
             Bytes wc[U];
             longlong2 qc[U];

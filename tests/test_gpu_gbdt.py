@@ -248,6 +248,31 @@ def test_degenerate_cases_bit_exact(case):
     np.testing.assert_array_equal(gm.view(np.uint32), wm.view(np.uint32))
 
 
+@pytest.mark.parametrize("depth", [1, 4])
+def test_no_rows_without_bins(depth):
+    """n_rows == 0 with null bins and margins and ld_bins 0, as the ABI allows: one leaf of value -0, no
+    row is read."""
+    require_gpu()
+    import torch
+    from paper_2211_11172_amd import harl
+    F, P, nodes = 11, 3, (1 << (depth + 1)) - 1
+    prm = harl.gbdt_params(max_depth=depth)
+    i32 = lambda v, n=nodes: torch.full((n,), v, dtype=torch.int32, device="cuda")
+    f32 = lambda v, n=nodes: torch.full((n,), v, device="cuda")
+    feature, thr, left, right, leaf = i32(77), f32(np.nan), i32(77), i32(77), f32(np.nan)
+    dleft = torch.full((nodes,), 7, dtype=torch.uint8, device="cuda")
+    wsb = harl.harl_gbdt_round_workspace_size(prm, F, 0, P)
+    ws = torch.full((wsb,), 0x5A, dtype=torch.uint8, device="cuda")
+    log("gbdt round without rows and bins: depth=%d" % depth)
+    harl.harl_gbdt_round(prm, None, 0, F, 0, f32(0.5, F), 1, i32(1, F), i32(0, P + 1), P, f32(1.0, P), f32(1.0, P), None,
+                         feature, thr, left, right, dleft, leaf, ws, wsb)
+    torch.cuda.synchronize()
+    assert (feature.cpu().numpy() == -1).all()
+    want = np.zeros(nodes, np.float32)
+    want[0] = -0.0
+    np.testing.assert_array_equal(leaf.cpu().numpy().view(np.uint32), want.view(np.uint32))
+
+
 def test_throughput_measured_set_full_size():
     """65,536 measured programs (2,134,518 rows), the benchmark's launch configuration (Ansor's
     settings, depth 10): bins bit-exact on every row; a depth-1 and the depth-10 round bit-exact
