@@ -522,7 +522,7 @@ int topk_launch(const float *score, int32_t n, int32_t k, int64_t index_base, fl
     if (k == 0 || (n == 0 && (flags & HARL_TOPK_MERGE))) return HARL_OK;
     const Plan p = make_plan(n, k);
     const size_t buf_bytes = round_up((int64_t)p.buf_keys * 8, 256);
-    if (ws_bytes < 2 * buf_bytes) return fail(HARL_E_WORKSPACE, "harl_topk: workspace too small");
+    if (ws_bytes < topk_ws_bytes(n, k)) return fail(HARL_E_WORKSPACE, "harl_topk: workspace too small");
     uint64_t *buf[2] = {static_cast<uint64_t *>(ws), reinterpret_cast<uint64_t *>(static_cast<char *>(ws) + buf_bytes)};
     const bool merge = flags & HARL_TOPK_MERGE;
     int32_t *counts = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + 2 * buf_bytes);  // kMaxLists words

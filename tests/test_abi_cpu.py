@@ -64,6 +64,10 @@ def test_topk_argument_errors():
     assert _status("harl_topk", None, 10, 5, 0, 0x1000, 0x2000, 0, 0x3000, 1 << 20, None) == harl.HARL_E_INVALID_ARG
     assert _status("harl_topk", 0x1000, 10, 5, 0, 0x1000, 0x2000, 0, 0x3000, 8, None) == harl.HARL_E_WORKSPACE
     assert _status("harl_topk", 0x1000, 10, 5, 0, 0x1000, 0x2000, 0, 0x3001, 1 << 20, None) == harl.HARL_E_INVALID_ARG
+    # the whole size is needed: the last words hold the lists' counts
+    for n, k, flags in ((10, 5, 0), (8193, 1, 0), (65536, 1024, 1), (131073, 2048, 1)):
+        need = harl.harl_topk_workspace_size(n, k)
+        assert _status("harl_topk", 0x1000, n, k, 0, 0x1000, 0x2000, flags, 0x3000, need - 1, None) == harl.HARL_E_WORKSPACE
     # k == 0 and (MERGE with n == 0) are valid no-ops
     assert _status("harl_topk", None, 0, 0, 0, None, None, 0, None, 0, None) == harl.HARL_OK
     assert _status("harl_topk", None, 0, 4, 0, 0x1000, 0x2000, 1, None, 0, None) == harl.HARL_OK
