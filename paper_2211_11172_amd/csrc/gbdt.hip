@@ -67,7 +67,12 @@ constexpr int kInPlaceRows = 4096;   // sets up to this size: every node one chu
 constexpr int kManyRows = 1 << 20;   // sets from this size: more chunks, 16 rows per partition thread
 constexpr int kMaxChunksInFlight = 98;  // histogram workgroups per feature group, at most
 constexpr int64_t kLineBytes = 96 << 20;  // bin bytes from which rows are laid out in lines
-constexpr int kQProgs = 32;          // programs per k_gb_row_q workgroup
+constexpr int kQProgs = 32;          // programs per k_gb_row_q workgroup and turn
+// Workgroups of programs in k_gb_start and k_gb_row_q, at most (they take more programs in turn): every
+// workgroup of the second reads the maxima of all of the first, so without a limit that work grew with
+// the square of the programs (16 M programs of one row, 8 features, a round of depth 6: 17.9 ms without the
+// limit, 4.4 with it), and beyond 2^29 programs the grid passed 2^32 threads.
+constexpr int kMaxProgBlocks = 2048;
 constexpr int kBinPasses = 16;       // passes over rows per binning workgroup, at most
 
 struct Params {
@@ -292,8 +297,8 @@ __global__ __launch_bounds__(kThreads) void k_gb_bin(const float *__restrict__ x
 // ------------------------------------------------------------------------------------------
 // gradients
 // ------------------------------------------------------------------------------------------
-// Blocks below nblk: per program of the block s_p, g_p, h_p and the block's maxima of |g|, |h|.  The
-// others: tree arrays to unreached-node defaults, node state cleared, the features' zero bins.
+// Blocks below nblk: per program s_p, g_p, h_p (a thread's programs nblk * kThreads apart) and the block's
+// maxima of |g|, |h|.  The others: tree arrays to unreached-node defaults, node state cleared, the features' zero bins.
 struct TreeOut {
     int32_t *feature;
     float *threshold;
@@ -335,9 +340,8 @@ __global__ __launch_bounds__(kThreads) void k_gb_start(const float *__restrict__
         }
         return;
     }
-    const int p = blockIdx.x * kThreads + threadIdx.x;
     double ag = 0.0, ah = 0.0;
-    if (p < P) {
+    for (int64_t p = (int64_t)blockIdx.x * kThreads + threadIdx.x; p < P; p += (int64_t)nblk * kThreads) {
         const int r0 = min(max(prog_ptr[p], 0), N), r1 = min(max(prog_ptr[p + 1], r0), N);
         double s = base;
         int r = r0;
@@ -354,8 +358,8 @@ __global__ __launch_bounds__(kThreads) void k_gb_start(const float *__restrict__
         w.gp[p] = g;
         w.hp[p] = h;
         if (r1 > r0) {
-            ag = fabs(g);
-            ah = fabs(h);
+            ag = fmax(ag, fabs(g));
+            ah = fmax(ah, fabs(h));
         }
     }
     sg[threadIdx.x] = ag;
@@ -375,7 +379,8 @@ __global__ __launch_bounds__(kThreads) void k_gb_start(const float *__restrict__
 }
 
 // The fixed-point exponents (every workgroup from the block maxima; workgroup 0 stores them) and the
-// integer pair of every row of the workgroup's 32 programs, row by row so that the stores coalesce.
+// integer pair of every row of the workgroup's 32 programs (several times 32 in turn), row by row so that
+// the stores coalesce.
 __global__ __launch_bounds__(kThreads) void k_gb_row_q(const int32_t *__restrict__ prog_ptr, int P, int N, int nblk,
                                                        Ws w) {
     __shared__ double sg[kThreads], sh[kThreads];
@@ -410,26 +415,28 @@ __global__ __launch_bounds__(kThreads) void k_gb_row_q(const int32_t *__restrict
         if (blockIdx.x == 0) w.exps[t] = e;
     }
     __syncthreads();
-    const int p0 = blockIdx.x * kQProgs, np = min(kQProgs, P - p0);
-    if (t < np) {
-        const int p = p0 + t;
-        qgs[t] = (int64_t)rint(ldexp(w.gp[p], se[0]));
-        qhs[t] = (int64_t)rint(ldexp(w.hp[p], se[1]));
-        const int r0 = min(max(prog_ptr[p], 0), N);  // clamped
-        first[t] = r0;
-        last[t] = min(max(prog_ptr[p + 1], r0), N);
-    }
-    __syncthreads();
-    if (np <= 0) return;
-    for (int r = first[0] + t; r < last[np - 1]; r += kThreads) {
-        int lo = 0, hi = np;  // the program whose rows hold r: the number of programs with last <= r
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (last[mid] <= r) lo = mid + 1;
-            else hi = mid;
+    for (int64_t p0 = (int64_t)blockIdx.x * kQProgs; p0 < P; p0 += (int64_t)gridDim.x * kQProgs) {
+        const int np = (int)min((int64_t)kQProgs, P - p0);
+        if (t < np) {
+            const int64_t p = p0 + t;
+            qgs[t] = (int64_t)rint(ldexp(w.gp[p], se[0]));
+            qhs[t] = (int64_t)rint(ldexp(w.hp[p], se[1]));
+            const int r0 = min(max(prog_ptr[p], 0), N);  // clamped
+            first[t] = r0;
+            last[t] = min(max(prog_ptr[p + 1], r0), N);
         }
-        lo = min(lo, np - 1);
-        w.q[r] = make_longlong2(qgs[lo], qhs[lo]);
+        __syncthreads();
+        for (int r = first[0] + t; r < last[np - 1]; r += kThreads) {
+            int lo = 0, hi = np;  // the program whose rows hold r: the number of programs with last <= r
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (last[mid] <= r) lo = mid + 1;
+                else hi = mid;
+            }
+            lo = min(lo, np - 1);
+            w.q[r] = make_longlong2(qgs[lo], qhs[lo]);
+        }
+        __syncthreads();  // the next turn rewrites the programs in LDS
     }
 }
 
@@ -1179,10 +1186,13 @@ Plan plan_for(int N, int F) {
     return p;
 }
 
+// Workgroups for P programs, `per` of them each in a turn.
+int prog_blocks(int P, int per) { return (int)std::min<int64_t>(ceil_div(std::max(P, 1), per), kMaxProgBlocks); }
+
 Ws carve(void *base, int F, int N, int P, int depth, size_t *total) {
     const int64_t n_nodes = ((int64_t)1 << (depth + 1)) - 1;
     const int64_t Lmax = (int64_t)1 << (depth - 1);  // widest level that builds histograms
-    const int64_t nblk = ceil_div(std::max(P, 1), kThreads);
+    const int64_t nblk = prog_blocks(P, kThreads);
     char *p = static_cast<char *>(base);
     size_t o = 0;
     auto take = [&](size_t bytes) {
@@ -1257,11 +1267,11 @@ int gbdt_round_launch(const harl_gbdt_params *prm_in, const uint8_t *bins, int64
     Ws w = carve(ws, F, N, P, D, &total);
     const Plan plan = plan_for(N, F);
     TreeOut tr{feature, threshold, left, right, default_left, leaf_value};
-    const int nblk = (int)ceil_div(std::max(P, 1), kThreads);
+    const int nblk = prog_blocks(P, kThreads);
     hipLaunchKernelGGL(k_gb_start, dim3((unsigned)(nblk + ceil_div(std::max(n_nodes, F), kThreads))), dim3(kThreads), 0,
                        stream, margin, prog_ptr, P, label, weight, prm.base, N, nblk, n_nodes, F, cuts, cut_stride, n_cuts,
                        w, tr);
-    hipLaunchKernelGGL(k_gb_row_q, dim3((unsigned)ceil_div(std::max(P, 1), kQProgs)), dim3(kThreads), 0, stream, prog_ptr, P, N, nblk, w);
+    hipLaunchKernelGGL(k_gb_row_q, dim3((unsigned)prog_blocks(P, kQProgs)), dim3(kThreads), 0, stream, prog_ptr, P, N, nblk, w);
     HARL_HIP_CHECK(hipGetLastError());
     HistArgs ha{bins, ld, F, n_fg, 0, D, N, 1, plan.seg_groups, plan.chunks, plan.keep_rows, cut_stride, n_cuts, prm};
     const int pchunk = N >= kManyRows ? 16 * kThreads : 4 * kThreads;

@@ -248,6 +248,31 @@ def test_degenerate_cases_bit_exact(case):
     np.testing.assert_array_equal(gm.view(np.uint32), wm.view(np.uint32))
 
 
+@pytest.mark.parametrize("P", [65537, 524289, 700001])
+def test_many_programs_bit_exact(P):
+    """More programs than the gradient kernels' workgroups take in one turn (65,536 and 524,288), among
+    them empty ones, with the largest gradient among the last programs."""
+    require_gpu()
+    rng = np.random.default_rng(P)
+    counts = rng.integers(0, 3, P)
+    counts[-1] = 2
+    ptr = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    N, F = int(ptr[-1]), 3
+    cuts = np.tile(np.arange(1, 6, dtype=np.float32), (F, 1))
+    n_cuts = np.full(F, 5, np.int32)
+    bins = np.zeros((N, _ld(F)), np.uint8)
+    bins[:, :F] = rng.integers(0, 6, (N, F))
+    label, weight = rng.random(P).astype(np.float32), rng.random(P).astype(np.float32)
+    label[-1], weight[-1] = -40.0, 3.0
+    m0 = rng.standard_normal(N).astype(np.float32)
+    log("gbdt round of %d programs, %d rows" % (P, N))
+    kw = dict(max_depth=3, gamma=0.0)
+    got, gm = gpu_rounds(bins, F, cuts, n_cuts, ptr, label, weight, m0, 1, **kw)
+    want, wm = oracle_rounds(bins, F, cuts, n_cuts, ptr, label, weight, m0, 1, **kw)
+    assert_trees_equal(got, want, "many programs")
+    np.testing.assert_array_equal(gm.view(np.uint32), wm.view(np.uint32))
+
+
 @pytest.mark.parametrize("depth", [1, 4])
 def test_no_rows_without_bins(depth):
     """n_rows == 0 with null bins and margins and ld_bins 0, as the ABI allows: one leaf of value -0, no
