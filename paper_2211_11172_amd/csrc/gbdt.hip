@@ -67,6 +67,8 @@ constexpr int kInPlaceRows = 4096;   // sets up to this size: every node one chu
 constexpr int kManyRows = 1 << 20;   // sets from this size: more chunks, 16 rows per partition thread
 constexpr int kMaxChunksInFlight = 98;  // histogram workgroups per feature group, at most
 constexpr int64_t kLineBytes = 96 << 20;  // bin bytes from which rows are laid out in lines
+constexpr int kMaxSegBlocks = 1 << 16;  // k_gb_segments workgroups per segment, at most (rows in turn): a
+                                     // thread per 16 bytes of 2^29 rows or more would pass 2^32 threads
 constexpr int kQProgs = 32;          // programs per k_gb_row_q workgroup and turn
 // Workgroups of programs in k_gb_start and k_gb_row_q, at most (they take more programs in turn): every
 // workgroup of the second reads the maxima of all of the first, so without a limit that work grew with
@@ -598,24 +600,24 @@ struct HistArgs {
 // and, in the last 16 bytes, the pair.  A row of a deep node then costs one cache line per segment
 // instead of one per feature group and one for the pair.
 __global__ __launch_bounds__(kThreads) void k_gb_segments(HistArgs a, Ws w) {
-    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;  // (row, 16-byte part)
-    const int64_t r = i / (kSegBytes / 16);
-    const int part = (int)(i % (kSegBytes / 16)), sgi = blockIdx.y;
-    if (r >= a.N) return;
-    uint64_t v[2] = {0, 0};
-    if (part == kSegBytes / 16 - 1) {
-        const longlong2 q = w.q[r];
-        v[0] = (uint64_t)q.x;
-        v[1] = (uint64_t)q.y;
-    } else {
+    constexpr int kParts = kSegBytes / 16;  // threads per line, 16 bytes each
+    const int part = threadIdx.x % kParts, sgi = blockIdx.y;
+    for (int64_t r = ((int64_t)blockIdx.x * kThreads + threadIdx.x) / kParts; r < a.N; r += (int64_t)gridDim.x * (kThreads / kParts)) {
+        uint64_t v[2] = {0, 0};
+        if (part == kParts - 1) {
+            const longlong2 q = w.q[r];
+            v[0] = (uint64_t)q.x;
+            v[1] = (uint64_t)q.y;
+        } else {
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            const int k = 2 * part + e, fg = sgi * a.seg_groups + k;
-            if (k < a.seg_groups && fg < a.n_fg)
-                v[e] = *reinterpret_cast<const uint64_t *>(a.bins + ((int64_t)fg * a.ld + r) * kGroup);
+            for (int e = 0; e < 2; ++e) {
+                const int k = 2 * part + e, fg = sgi * a.seg_groups + k;
+                if (k < a.seg_groups && fg < a.n_fg)
+                    v[e] = *reinterpret_cast<const uint64_t *>(a.bins + ((int64_t)fg * a.ld + r) * kGroup);
+            }
         }
+        *reinterpret_cast<ulonglong2 *>(w.seg + ((int64_t)sgi * a.N + r) * kSegBytes + part * 16) = make_ulonglong2(v[0], v[1]);
     }
-    *reinterpret_cast<ulonglong2 *>(w.seg + ((int64_t)sgi * a.N + r) * kSegBytes + part * 16) = make_ulonglong2(v[0], v[1]);
 }
 
 // Workgroup = (chunk c, feature group fg) of the level's built nodes, several in turn.  Every
@@ -1282,7 +1284,9 @@ int gbdt_round_launch(const harl_gbdt_params *prm_in, const uint8_t *bins, int64
         ha.hx = (int)hx;
         if (d > 0 && plan.n_seg > 0) {
             if (d == 1)
-                hipLaunchKernelGGL(k_gb_segments, dim3((unsigned)ceil_div((int64_t)N * (kSegBytes / 16), kThreads), (unsigned)plan.n_seg),
+                hipLaunchKernelGGL(k_gb_segments,
+                                   dim3((unsigned)std::min<int64_t>(ceil_div((int64_t)N * (kSegBytes / 16), kThreads), kMaxSegBlocks),
+                                        (unsigned)plan.n_seg),
                                    dim3(kThreads), 0, stream, ha, w);
             hipLaunchKernelGGL(k_gb_hist<true>, dim3((unsigned)(round_up((int64_t)hx * plan.n_seg, 8) * plan.seg_groups)),
                                dim3(kThreads), 0, stream, ha, w);
