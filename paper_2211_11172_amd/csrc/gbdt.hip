@@ -65,7 +65,6 @@ constexpr int kFeatWords = 2 * kBins;  // int64 words of one feature of a stored
 constexpr int kMinChunk = 512;       // rows of a histogram chunk, at least
 constexpr int kInPlaceRows = 4096;   // sets up to this size: every node one chunk, evaluated in place
 constexpr int kManyRows = 1 << 20;   // sets from this size: more chunks, 16 rows per partition thread
-constexpr int kMaxChunksInFlight = 98;  // histogram workgroups per feature group, at most
 constexpr int64_t kLineBytes = 96 << 20;  // bin bytes from which rows are laid out in lines
 constexpr int kMaxSegBlocks = 1 << 16;  // k_gb_segments workgroups per segment, at most (rows in turn): a
                                      // thread per 16 bytes of 2^29 rows or more would pass 2^32 threads
@@ -1160,15 +1159,22 @@ struct Plan {
     int n_seg, seg_groups;  // segments of the row lines (0: none)
 };
 
+// Histogram workgroups of a level, about: the chunks that its rows are cut into times the feature groups,
+// and the most workgroups that are launched (each takes several chunks in turn, and one that has none
+// still works out the chunk list).  Three fit a CU (146 registers a thread): 768 are one full machine,
+// which is also enough for small sets, whose partials cost as much as their rows; from kManyRows on the
+// finer cut of 1,024 pays (2.1 M rows x 164 features, a round: 1,454 us with 768 of them in flight, 1,386
+// with 1,024).  One round of depth 10, with up to 98 chunks of every feature group in flight and now:
+// 2.1 M rows x 8 features 913 -> 721 us, x 32 features 845 -> 852; 68,000 rows x 164 features 249 -> 227;
+// 5,000 rows x 4,096 features 1,787 -> 1,248.
+int hist_blocks(int N) { return N >= kManyRows ? 1024 : 768; }
+
 Plan plan_for(int N, int F) {
     const int n_fg = (F + kGroup - 1) / kGroup;
     Plan p;
-    // about 1,024 (chunk, feature group) workgroups on large sets (four fit a CU's LDS), fewer on small
-    // ones, whose partials cost as much as their rows (68,182 rows, four rounds: 1,567 us with 768
-    // workgroups against 1,622 with 1,024; 2.12 M rows, two rounds: 4.38 against 4.16 ms)
     p.chunks = 1;
     if (N > kInPlaceRows) {
-        p.chunks = std::max(2, (N >= kManyRows ? 1024 : 768) / n_fg);
+        p.chunks = std::max(2, hist_blocks(N) / n_fg);
         p.chunks = std::min(p.chunks, (N + kMinChunk - 1) / kMinChunk);
     }
     // keeping and subtracting a node's histogram moves about as many bytes as building 4,096 rows; at
@@ -1280,7 +1286,9 @@ int gbdt_round_launch(const harl_gbdt_params *prm_in, const uint8_t *bins, int64
     for (int d = 0; d < D; ++d) {
         const int64_t L = std::min<int64_t>((int64_t)1 << d, std::max(N, 1));
         ha.d = d;
-        const unsigned hx = (unsigned)std::min<int64_t>(d == 0 ? plan.chunks : 2 * plan.chunks + L, kMaxChunksInFlight);
+        // chunks in flight: a level has about plan.chunks of them or, where it is deeper than that, a chunk or
+        // less per node
+        const unsigned hx = (unsigned)std::min<int64_t>(std::max<int64_t>(plan.chunks, L), ceil_div(hist_blocks(N), n_fg));
         ha.hx = (int)hx;
         if (d > 0 && plan.n_seg > 0) {
             if (d == 1)

@@ -168,6 +168,8 @@ def test_rounds_bit_exact(name, n_prog, s_max, F, depth, p_nan, rounds):
     ("ragged groups, missing values", 6000, 9, 13, 8, 0.3, 25000),
     # so many feature groups that a level is cut into two chunks only
     ("most features", 1500, 5, 4096, 3, 0.1, 4097),
+    # one feature group cut into 1,024 chunks, all in flight
+    ("few features, many rows", 66000, 32, 8, 6, 0.1, 1 << 20),
 ])
 def test_histogram_routes_bit_exact(name, n_prog, s_max, F, depth, p_nan, min_rows):
     require_gpu()
