@@ -65,7 +65,8 @@ constexpr int kFeatWords = 2 * kBins;  // int64 words of one feature of a stored
 constexpr int kMinChunk = 512;       // rows of a histogram chunk, at least
 constexpr int kInPlaceRows = 4096;   // sets up to this size: every node one chunk, evaluated in place
 constexpr int kManyRows = 1 << 20;   // sets from this size: more chunks, 16 rows per partition thread
-constexpr int64_t kLineBytes = 96 << 20;  // bin bytes from which rows are laid out in lines
+constexpr int64_t kLineBytes = 96 << 20;  // bin bytes, rows and feature groups from which rows are laid
+constexpr int kLineRows = 1 << 19, kLineGroups = 3;  // out in lines (see plan_for)
 constexpr int kMaxSegBlocks = 1 << 16;  // k_gb_segments workgroups per segment, at most (rows in turn): a
                                      // thread per 16 bytes of 2^29 rows or more would pass 2^32 threads
 constexpr int kQProgs = 32;          // programs per k_gb_row_q workgroup and turn
@@ -1186,9 +1187,13 @@ Plan plan_for(int N, int F) {
     // fewer than 2 chunks' worth of pieces in all, and the kept nodes' smaller children one each
     p.slots = p.chunks == 1 ? 1 : N / p.keep_rows + 1;
     p.pmax = p.chunks == 1 ? 1 : 2 * p.chunks + p.slots;
-    // laying out the lines reads and writes the bins once (170 us at 2.12 M rows); two rounds with and
-    // without: 90 MB of bins 1.61 / 1.63 ms, 178 MB 2.48 / 2.69 ms, 357 MB 4.13 / 5.57 ms
-    const bool lines = (int64_t)N * n_fg * kGroup >= kLineBytes;
+    // Lines pay where a node's rows are spread over more memory than the caches hold and where a line has
+    // enough in it: bins of a group beyond an XCD's 4 MB L2 (from 2^19 rows), bins in all beyond
+    // kLineBytes, and three groups or more (one: 24 of 128 bytes used, and a workspace of 128 bytes a row).
+    // One round of depth 10 without and with them, in us: 100 MB of bins as 1 group 2,943 / 3,355, 2:
+    // 1,713 / 1,795, 3: 1,350 / 1,288, 8: 923 / 740, 21: 623 / 605; of 437,000 rows x 30 groups 530 / 539;
+    // 204,000 x 64 421 / 479; 200 MB as 4 groups 2,349 / 1,917, 21: 1,215 / 945, 409,000 x 64 799 / 817.
+    const bool lines = (int64_t)N * n_fg * kGroup >= kLineBytes && N >= kLineRows && n_fg >= kLineGroups;
     p.n_seg = lines ? (n_fg + kSegGroups - 1) / kSegGroups : 0;
     p.seg_groups = lines ? (n_fg + p.n_seg - 1) / p.n_seg : 1;
     return p;

@@ -250,6 +250,31 @@ def test_degenerate_cases_bit_exact(case):
     np.testing.assert_array_equal(gm.view(np.uint32), wm.view(np.uint32))
 
 
+# rows laid out in lines: one segment (its last group ragged), and three of which the last is not full;
+# below them the sets that take no lines for their rows or their few groups
+@pytest.mark.parametrize("F,N", [(105, 900001), (241, 524289), (241, 524287), (16, 6300001)])
+def test_row_lines_bit_exact(F, N):
+    require_gpu()
+    rng = np.random.default_rng(F)
+    cuts = np.tile(np.arange(1, 31, dtype=np.float32), (F, 1))
+    n_cuts = np.full(F, 30, np.int32)
+    bins = np.zeros((N, _ld(F)), np.uint8)
+    bins[:, :F] = rng.integers(0, 31, (N, F), dtype=np.uint8)
+    bins[rng.random(N) < 0.2, F // 2] = 255
+    ptr = np.arange(0, N + 16, 16, dtype=np.int32).clip(max=N)
+    P = len(ptr) - 1
+    weight = rng.random(P).astype(np.float32)
+    label = ((bins[ptr[:-1], 0] > 20) + 0.5 * (bins[ptr[:-1], F - 1] > 9) + 0.1 * rng.random(P)).astype(np.float32)
+    m0 = np.zeros(N, np.float32)
+    kw = dict(max_depth=4, gamma=0.0)
+    log("gbdt row lines: F=%d rows=%d" % (F, N))
+    got, gm = gpu_rounds(bins, F, cuts, n_cuts, ptr, label, weight, m0, 1, **kw)
+    want, wm = oracle_rounds(bins, F, cuts, n_cuts, ptr, label, weight, m0, 1, **kw)
+    assert (want[0]["feature"] >= 0).sum() >= 8
+    assert_trees_equal(got, want, "row lines")
+    np.testing.assert_array_equal(gm.view(np.uint32), wm.view(np.uint32))
+
+
 @pytest.mark.parametrize("P", [65537, 524289, 700001])
 def test_many_programs_bit_exact(P):
     """More programs than the gradient kernels' workgroups take in one turn (65,536 and 524,288), among
