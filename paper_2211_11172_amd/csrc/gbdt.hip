@@ -65,6 +65,12 @@ constexpr int kFeatWords = 2 * kBins;  // int64 words of one feature of a stored
 constexpr int kMinChunk = 512;       // rows of a histogram chunk, at least
 constexpr int kInPlaceRows = 4096;   // sets up to this size: every node one chunk, evaluated in place
 constexpr int kManyRows = 1 << 20;   // sets from this size: more chunks, 16 rows per partition thread
+// Histogram workgroups of a level below the root, about, at most: three for each that the machine holds,
+// which take several chunks in turn and even out chunks of different sizes (trees of thousands of nodes,
+// 68,000 rows x 164 features: 1,321 us a round with 768, 1,179 with 1,536, 1,149 with 2,304; 2,058 up to
+// 98 for each of the 21 feature groups: 1,131).  A cap per feature group is none for the machine: with 98
+// each, 2.1 M rows x 8 features took 917 us and now 732; 5,000 rows x 4,096 features 1,779 and now 1,182.
+constexpr int kMaxHistBlocks = 2304;
 constexpr int64_t kLineBytes = 96 << 20;  // bin bytes, rows and feature groups from which rows are laid
 constexpr int kLineRows = 1 << 19, kLineGroups = 3;  // out in lines (see plan_for)
 constexpr int kMaxSegBlocks = 1 << 16;  // k_gb_segments workgroups per segment, at most (rows in turn): a
@@ -99,6 +105,7 @@ struct Ws {
     uint64_t *nlr;               // per heap node: rows moved left | rows moved right << 32
     int32_t *pbase, *nparts;     // level: first partial of a node and their number
     int32_t *list, *lvl;         // level: the nodes k_gb_split evaluates, and their number
+    int32_t *alive;              // per level: nodes whose parent was split
     int32_t *zb;                 // [F] the bin of 0.0 per feature
     Best *best;                  // level: [2^d][F]
     int64_t *part, *hist[2];     // [pmax], [slots] by level parity: histograms [F][G|H][kBins]
@@ -313,8 +320,8 @@ __global__ __launch_bounds__(kThreads) void k_gb_start(const float *__restrict__
                                                        const int32_t *__restrict__ prog_ptr, int P,
                                                        const float *__restrict__ label,
                                                        const float *__restrict__ weight, double base, int N, int nblk,
-                                                       int n_nodes, int F, const float *__restrict__ cuts,
-                                                       int cut_stride, const int32_t *__restrict__ n_cuts, Ws w,
+                                                       int n_nodes, int levels, int F,
+                                                       const float *__restrict__ cuts, int cut_stride, const int32_t *__restrict__ n_cuts, Ws w,
                                                        TreeOut tr) {
     __shared__ double sg[kThreads], sh[kThreads];
     if ((int)blockIdx.x >= nblk) {
@@ -330,6 +337,7 @@ __global__ __launch_bounds__(kThreads) void k_gb_start(const float *__restrict__
             w.rank[i] = -1;
             w.nlr[i] = 0;
         }
+        if (i < levels) w.alive[i] = 0;
         if (i < F) {  // the bin of 0.0: the number of cut points <= 0
             const float *cf = cuts + (int64_t)i * cut_stride;
             int lo = 0, hi = clamp_cuts(n_cuts, i, cut_stride);
@@ -621,7 +629,7 @@ __global__ __launch_bounds__(kThreads) void k_gb_segments(HistArgs a, Ws w) {
 }
 
 // Workgroup = (chunk c, feature group fg) of the level's built nodes, several in turn.  Every
-// workgroup works out the level's chunk list from the parents' partition by itself (a scan over at
+// workgroup that can have a chunk works out the level's chunk list from the parents' partition by itself (a scan over at
 // most 2^d nodes, cheaper than a launch of its own); workgroup (0, 0) stores it for the kernels that
 // follow.
 template <bool SEG>
@@ -649,6 +657,9 @@ __global__ __launch_bounds__(kThreads, 3) void k_gb_hist(HistArgs a, Ws w) {
         bx = blockIdx.x / n_fg;
         nbx = a.hx;
     }
+    // a level has at most a chunk per node more than the a.chunks its rows are cut into: the others leave
+    // before they work out the chunk list
+    if (bx >= a.chunks && bx >= a.chunks + w.alive[a.d]) return;
     const int f0 = fg * kGroup;
     const int nf = std::min(kGroup, a.F - f0);
     if (t < kGroup) {
@@ -1096,6 +1107,7 @@ __global__ __launch_bounds__(kThreads) void k_gb_part(HistArgs a, Ws w, const fl
                 tr.leaf_value[2 * k + 2] = vr;
             }
             w.sf[k] = f;
+            if (!last) atomicAdd(&w.alive[a.d + 1], 2);
         }
         const uint8_t *__restrict__ bf = a.bins + (int64_t)(f / kGroup) * a.ld * kGroup + f % kGroup;
         uint32_t b[R], left = 0;
@@ -1160,14 +1172,10 @@ struct Plan {
     int n_seg, seg_groups;  // segments of the row lines (0: none)
 };
 
-// Histogram workgroups of a level, about: the chunks that its rows are cut into times the feature groups,
-// and the most workgroups that are launched (each takes several chunks in turn, and one that has none
-// still works out the chunk list).  Three fit a CU (146 registers a thread): 768 are one full machine,
-// which is also enough for small sets, whose partials cost as much as their rows; from kManyRows on the
-// finer cut of 1,024 pays (2.1 M rows x 164 features, a round: 1,454 us with 768 of them in flight, 1,386
-// with 1,024).  One round of depth 10, with up to 98 chunks of every feature group in flight and now:
-// 2.1 M rows x 8 features 913 -> 721 us, x 32 features 845 -> 852; 68,000 rows x 164 features 249 -> 227;
-// 5,000 rows x 4,096 features 1,787 -> 1,248.
+// Chunks that a level's rows are cut into, times the feature groups.  Three histogram workgroups fit a CU
+// (146 registers a thread): 768 are one full machine, which is also enough for small sets, whose partials
+// cost as much as their rows; from kManyRows on the finer cut of 1,024 pays (2.1 M rows x 164 features, a
+// round of depth 10: 1,454 us with 768, 1,386 with 1,024).
 int hist_blocks(int N) { return N >= kManyRows ? 1024 : 768; }
 
 Plan plan_for(int N, int F) {
@@ -1230,6 +1238,7 @@ Ws carve(void *base, int F, int N, int P, int depth, size_t *total) {
     w.nparts = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * Lmax));
     w.list = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * Lmax));
     w.lvl = reinterpret_cast<int32_t *>(take(sizeof(int32_t)));
+    w.alive = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * (depth + 1)));
     w.zb = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * F));
     w.best = reinterpret_cast<Best *>(take(sizeof(Best) * Lmax * F));
     const Plan plan = plan_for(N, F);
@@ -1282,7 +1291,7 @@ int gbdt_round_launch(const harl_gbdt_params *prm_in, const uint8_t *bins, int64
     TreeOut tr{feature, threshold, left, right, default_left, leaf_value};
     const int nblk = prog_blocks(P, kThreads);
     hipLaunchKernelGGL(k_gb_start, dim3((unsigned)(nblk + ceil_div(std::max(n_nodes, F), kThreads))), dim3(kThreads), 0,
-                       stream, margin, prog_ptr, P, label, weight, prm.base, N, nblk, n_nodes, F, cuts, cut_stride, n_cuts,
+                       stream, margin, prog_ptr, P, label, weight, prm.base, N, nblk, n_nodes, D + 1, F, cuts, cut_stride, n_cuts,
                        w, tr);
     hipLaunchKernelGGL(k_gb_row_q, dim3((unsigned)prog_blocks(P, kQProgs)), dim3(kThreads), 0, stream, prog_ptr, P, N, nblk, w);
     HARL_HIP_CHECK(hipGetLastError());
@@ -1291,9 +1300,7 @@ int gbdt_round_launch(const harl_gbdt_params *prm_in, const uint8_t *bins, int64
     for (int d = 0; d < D; ++d) {
         const int64_t L = std::min<int64_t>((int64_t)1 << d, std::max(N, 1));
         ha.d = d;
-        // chunks in flight: a level has about plan.chunks of them or, where it is deeper than that, a chunk or
-        // less per node
-        const unsigned hx = (unsigned)std::min<int64_t>(std::max<int64_t>(plan.chunks, L), ceil_div(hist_blocks(N), n_fg));
+        const unsigned hx = (unsigned)(d == 0 ? plan.chunks : std::min<int64_t>(2 * plan.chunks + L, ceil_div(kMaxHistBlocks, n_fg)));
         ha.hx = (int)hx;
         if (d > 0 && plan.n_seg > 0) {
             if (d == 1)
