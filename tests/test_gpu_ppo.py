@@ -119,7 +119,9 @@ def test_ppo_update_odd_shapes_and_segments():
 # row tiles of 128, 64 and 32 with a ragged last one, column tiles of 64 and 32, K not a multiple of a
 # stage, rows that no multiple of 4 divides (the transposed operands), a head of one tile and of two
 @pytest.mark.parametrize("M,dims", [(43661, (36, 132, 196, 30)), (16385, (4, 68, 260, 31)), (4097, (8, 36, 100, 33)),
-                                    (127, (64, 256, 256, 26))])
+                                    (127, (64, 256, 256, 26)),
+                                    # wide layers: products of one and of three pieces, tiles that 8 does not divide
+                                    (65, (12, 520, 1024, 40)), (300, (64, 1024, 1000, 26))])
 def test_ppo_update_tile_edges(M, dims):
     require_gpu()
     segs = [0, 3, dims[3] - 4, dims[3]]
