@@ -681,14 +681,15 @@ int gemm(const GemmArgs &g0, float *partial, hipStream_t stream) {
     float *out = g.C;
     if (g.split) g.C = partial;
     // the largest tile that leaves the machine at least four workgroups per CU (what its registers
-    // let a CU hold); tiles of 32 also where C has no more rows or columns (the head's product of
-    // 65,536 rows and 26 columns: 30 us on tiles of 64 columns, 19.5 on 32)
+    // let a CU hold), but none taller or wider than C's last rows and columns need: tiles of 32 columns for
+    // a head (65,536 rows x 26 columns: 30 us on tiles of 64 columns, 19.5 on 32), tiles of 32 or 64 rows
+    // for its weight gradient (28 rows x 2,048 of 16,384 transitions: 92 us on tiles of 128 rows, 31 on 32)
     auto fills = [&](int ti, int tj) { return ceil_div(J0, tj) * ceil_div(g.I, ti) * used >= 1024; };
     if (vec) {
         if (J0 <= 32) {
             if (fills(64, 32)) launch_gemm_v<64, 32, 64>(g, used, stream);
             else launch_gemm_v<32, 32, 64>(g, used, stream);
-        } else if (fills(128, 64)) {
+        } else if (fills(128, 64) && g.I > 64) {
             launch_gemm_v<128, 64, 32>(g, used, stream);
         } else if (fills(64, 64) && g.I > 32) {
             launch_gemm_v<64, 64, 64>(g, used, stream);

@@ -121,7 +121,11 @@ def test_ppo_update_odd_shapes_and_segments():
 @pytest.mark.parametrize("M,dims", [(43661, (36, 132, 196, 30)), (16385, (4, 68, 260, 31)), (4097, (8, 36, 100, 33)),
                                     (127, (64, 256, 256, 26)),
                                     # wide layers: products of one and of three pieces, tiles that 8 does not divide
-                                    (65, (12, 520, 1024, 40)), (300, (64, 1024, 1000, 26))])
+                                    (65, (12, 520, 1024, 40)), (300, (64, 1024, 1000, 26)),
+                                    # a head's weight gradient (28 rows) of enough columns and pieces for tall tiles
+                                    (16421, (8, 36, 512, 26)),
+                                    # row tiles of 64 with column tiles of 32, the last one ragged, both stores
+                                    (65573, (8, 32, 36, 30)), (65573, (8, 32, 36, 28))])
 def test_ppo_update_tile_edges(M, dims):
     require_gpu()
     segs = [0, 3, dims[3] - 4, dims[3]]
