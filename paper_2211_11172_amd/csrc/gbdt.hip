@@ -46,6 +46,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "internal.hpp"
 
@@ -178,13 +179,16 @@ __device__ __forceinline__ void best_lanes(int &bv, double &bg, int &bk, int64_t
 // ------------------------------------------------------------------------------------------
 // Workgroup = (8-feature group, range of rows).  Per feature a table of 256 buckets of the cut points'
 // order-preserving keys is built in LDS first: bucket -> how many cut points lie in lower buckets and
-// how many up to it, so a value starts its binary search with the cut points of its own bucket alone
-// (`steps` probes, for the fullest bucket of the group: 2 for cut points spread over the keys, 8 at
-// most).  The bucket is any monotone function of the key, the same for cut points and values, so the
-// result is the plain count of cut points <= x; -0 counts as +0.  A thread codes two rows of the
-// group, whose 16 searches overlap.
-// 2.12 M rows x 164 features: 790 us with searches over all cut points (8 probes), 460 us now, 3.8
-// TB/s of the features and bins; the probes' LDS reads and the address arithmetic bound it.
+// how many up to it, so a value starts its binary search with the cut points of its own bucket alone.
+// A search takes `steps` probes, as many as the fullest bucket of the group needs: 2 or 3 where the cut
+// points are spread over the keys, 4 for 152 of them over six decades and one at 0.0 (which stretches the
+// window so that a bucket is an octave), 8 at most.  The bucket is any monotone function of the key, the
+// same for cut points and values, so the result is the plain count of cut points <= x; -0 counts as +0.
+// A thread codes two rows of the group, whose 16 searches overlap; the first rows are loaded while the
+// table is built, which 32 lanes per feature do by counting (1 us; a search per bucket took 9).
+// 2.1 M rows x 164 features: 760 us with searches over all cut points (8 probes), 400 us now, 4.3 TB/s of
+// the features and bins; the probes' LDS reads and the address arithmetic bound it.  16,384 rows x 164
+// features: 10.3 us then, 10.7 now.
 __device__ __forceinline__ uint32_t bin_key(float v) {
     const uint32_t u = __float_as_uint(v + 0.f);  // -0 + 0 = +0
     return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
@@ -203,54 +207,79 @@ __global__ __launch_bounds__(kThreads) void k_gb_bin(const float *__restrict__ x
                                                      const int32_t *__restrict__ n_cuts, uint8_t *__restrict__ bins,
                                                      int64_t ld, int passes) {
     __shared__ float sc[kGroup][kCutStride];
-    __shared__ uint16_t lut[kGroup][256];  // cut points in lower buckets | up to this one << 8
-    __shared__ uint8_t cb[kGroup][256];    // bucket of every cut point
+    __shared__ __attribute__((aligned(16))) uint16_t lut[kGroup][256];  // cut points in lower buckets | up to this one << 8
+    __shared__ uint32_t cnt[kGroup][64];  // cut points per bucket, a byte each
     __shared__ int snc[kGroup], ssh[kGroup], full;
     __shared__ uint32_t sbase[kGroup];
     const int g = blockIdx.y, t = threadIdx.x;
     const int nf = min(kGroup, F - g * kGroup);
-    if (t < kGroup) {
-        const int nc = t < nf ? clamp_cuts(n_cuts, g * kGroup + t, cut_stride) : 0;
-        snc[t] = nc;
-        uint32_t base = 0;
-        int sh = 0;
-        if (nc > 0) {
-            const float *c = cuts + (int64_t)(g * kGroup + t) * cut_stride;
-            const uint32_t k0 = bin_key(c[0]), k1 = bin_key(c[nc - 1]), span = k1 > k0 ? k1 - k0 : 0u;
-            while ((span >> sh) > 253u) ++sh;
-            base = k0 > (1u << sh) ? k0 - (1u << sh) : 0u;  // the first cut point in bucket 1
-        }
-        sbase[t] = base;
-        ssh[t] = sh;
-    }
+    const float *__restrict__ xg = x + (int64_t)g * kGroup * ldx;
+    const int r_first = blockIdx.x * passes * kThreads * kBinRows + t;
+    float v[kBinRows][kGroup];
+    // the last group of 8 may have fewer features: those past F are neither read nor searched nor stored
+    auto fetch = [&](int r0) {  // rows past N are clamped and not stored
+#pragma unroll
+        for (int j = 0; j < kGroup; ++j)
+            if (j < nf)
+#pragma unroll
+                for (int q = 0; q < kBinRows; ++q) v[q][j] = xg[(int64_t)j * ldx + min(r0 + q * kThreads, N - 1)];
+    };
+    fetch(r_first);  // in flight while the table is built
+    if (t < kGroup) snc[t] = t < nf ? clamp_cuts(n_cuts, g * kGroup + t, cut_stride) : 0;
     if (t == 0) full = 0;
+    (&cnt[0][0])[t] = 0;
+    (&cnt[0][0])[t + kThreads] = 0;
     __syncthreads();
     for (int e = t; e < kGroup * kCutStride; e += kThreads) {
         const int j = e / kCutStride, i = e % kCutStride;
-        const float v = i < snc[j] ? cuts[(int64_t)(g * kGroup + j) * cut_stride + i] : NAN;
-        sc[j][i] = v;
-        if (i < snc[j]) cb[j][i] = (uint8_t)bin_bucket(v, sbase[j], ssh[j]);
+        sc[j][i] = i < snc[j] ? cuts[(int64_t)(g * kGroup + j) * cut_stride + i] : NAN;
     }
     __syncthreads();
-    int most = 0;
-#pragma unroll 1
-    for (int j = 0; j < nf; ++j) {  // thread t: bucket t
-        int lo = 0, hi = snc[j];
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (cb[j][mid] < t) lo = mid + 1;
-            else hi = mid;
+    {  // 32 lanes per feature: its window, its cut points counted per bucket, then their prefix sums
+        const int j = t / 32, q = t % 32, nc = snc[j];
+        uint32_t base = 0;
+        int sh = 0;
+        if (nc > 0) {
+            const uint32_t k0 = bin_key(sc[j][0]), k1 = bin_key(sc[j][nc - 1]), span = k1 > k0 ? k1 - k0 : 0u;
+            sh = max(0, 24 - __builtin_clz(span | 1u));
+            sh += (span >> sh) > 253u;
+            base = k0 > (1u << sh) ? k0 - (1u << sh) : 0u;  // the first cut point in bucket 1
         }
-        int up = lo, top = snc[j];
-        while (up < top) {
-            const int mid = (up + top) >> 1;
-            if (cb[j][mid] <= t) up = mid + 1;
-            else top = mid;
+        for (int i = q; i < nc; i += 32) {
+            const uint32_t b = bin_bucket(sc[j][i], base, sh);
+            atomicAdd(&cnt[j][b / 4], 1u << (8 * (b % 4)));
         }
-        lut[j][t] = (uint16_t)(lo | up << 8);
-        most = max(most, up - lo);
+        if (q == 0) {
+            sbase[j] = base;
+            ssh[j] = sh;
+        }
+        __syncthreads();
+        const uint32_t c[2] = {cnt[j][2 * q], cnt[j][2 * q + 1]};
+        int n[8], sum = 0, most = 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            n[e] = (int)((c[e / 4] >> (8 * (e % 4))) & 255u);
+            sum += n[e];
+            most = max(most, n[e]);
+        }
+        int before = sum;
+#pragma unroll
+        for (int off = 1; off < 32; off <<= 1) {
+            const int o = __shfl_up(before, off, 32);
+            if (q >= off) before += o;
+            most = max(most, __shfl_xor(most, off, 32));
+        }
+        before -= sum;
+        uint32_t e2[4];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const uint32_t w = (uint32_t)before | (uint32_t)(before + n[e]) << 8;
+            e2[e / 2] = e % 2 ? e2[e / 2] | w << 16 : w;
+            before += n[e];
+        }
+        *reinterpret_cast<uint4 *>(&lut[j][8 * q]) = make_uint4(e2[0], e2[1], e2[2], e2[3]);
+        if (q == 0 && most > 0) atomicMax(&full, most);
     }
-    if (most > 0) atomicMax(&full, most);
     __syncthreads();
     const int steps = 32 - __builtin_clz(full | 1) - (full == 0);  // 2^steps > full
     uint32_t base[kGroup];
@@ -260,46 +289,46 @@ __global__ __launch_bounds__(kThreads) void k_gb_bin(const float *__restrict__ x
         base[j] = sbase[j];
         sh[j] = ssh[j];
     }
-    const float *__restrict__ xg = x + (int64_t)g * kGroup * ldx;
-    for (int ps = 0; ps < passes; ++ps) {
-        const int r0 = (blockIdx.x * passes + ps) * kThreads * kBinRows + t;
-        if (r0 - t >= N) return;
-        float v[kBinRows][kGroup];
+    auto bin_rows = [&](auto all, int r0) {
+        constexpr bool ALL = decltype(all)::value;  // 8 features
         int lo[kBinRows][kGroup], hi[kBinRows][kGroup];
 #pragma unroll
-        for (int q = 0; q < kBinRows; ++q)
+        for (int j = 0; j < kGroup; ++j)
+            if (ALL || j < nf)
 #pragma unroll
-            for (int j = 0; j < kGroup; ++j)  // clamped: rows past N and features past F are not stored
-                v[q][j] = xg[(int64_t)min(j, nf - 1) * ldx + min(r0 + q * kThreads, N - 1)];
-#pragma unroll
-        for (int q = 0; q < kBinRows; ++q)
-#pragma unroll
-            for (int j = 0; j < kGroup; ++j) {
-                const uint32_t e = lut[j][bin_bucket(v[q][j], base[j], sh[j])];
-                lo[q][j] = (int)(e & 255u);
-                hi[q][j] = (int)(e >> 8);
-            }
+                for (int q = 0; q < kBinRows; ++q) {
+                    const uint32_t e = lut[j][bin_bucket(v[q][j], base[j], sh[j])];
+                    lo[q][j] = (int)(e & 255u);
+                    hi[q][j] = (int)(e >> 8);
+                }
         for (int s = 0; s < steps; ++s)  // a finished search stays: its next cut point is > v (or the NaN after the last)
 #pragma unroll
-            for (int q = 0; q < kBinRows; ++q)
+            for (int j = 0; j < kGroup; ++j)
+                if (ALL || j < nf)
 #pragma unroll
-                for (int j = 0; j < kGroup; ++j) {
-                    const int mid = (lo[q][j] + hi[q][j]) >> 1;
-                    const bool up = sc[j][mid] <= v[q][j];
-                    lo[q][j] = up ? mid + 1 : lo[q][j];
-                    hi[q][j] = up ? hi[q][j] : mid;
-                }
+                    for (int q = 0; q < kBinRows; ++q) {
+                        const int mid = (lo[q][j] + hi[q][j]) >> 1;
+                        const bool up = sc[j][mid] <= v[q][j];
+                        lo[q][j] = up ? mid + 1 : lo[q][j];
+                        hi[q][j] = up ? hi[q][j] : mid;
+                    }
 #pragma unroll
         for (int q = 0; q < kBinRows; ++q) {
             uint32_t w[2] = {0, 0};
 #pragma unroll
-            for (int j = 0; j < kGroup; ++j) {
-                const uint32_t b = v[q][j] != v[q][j] ? 255u : (uint32_t)min(lo[q][j], 254);
-                if (j < nf) w[j / 4] |= b << (8 * (j % 4));
-            }
+            for (int j = 0; j < kGroup; ++j)
+                if (ALL || j < nf)
+                    w[j / 4] |= (v[q][j] != v[q][j] ? 255u : (uint32_t)min(lo[q][j], 254)) << (8 * (j % 4));
             const int r = r0 + q * kThreads;
             if (r < N) *reinterpret_cast<uint2 *>(bins + ((int64_t)g * ld + r) * kGroup) = make_uint2(w[0], w[1]);
         }
+    };
+    for (int ps = 0; ps < passes; ++ps) {
+        const int r0 = r_first + ps * kThreads * kBinRows;
+        if (r0 - t >= N) return;
+        if (ps > 0) fetch(r0);
+        if (nf == kGroup) bin_rows(std::true_type{}, r0);
+        else bin_rows(std::false_type{}, r0);
     }
 }
 

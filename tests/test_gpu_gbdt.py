@@ -139,6 +139,35 @@ def test_bins_bit_exact(F, n_cuts, p_nan):
     assert (planes[:, m["n_rows"]:, :] == 0xAB).all(), "rows past n_rows must not be written"
 
 
+@pytest.mark.parametrize("F,rows", [(1, 1), (9, 513), (16, 1024), (23, 30001)])
+def test_bins_of_uneven_cut_points(F, rows):
+    """Cut points that the bucket table separates badly or at the ends of its range: almost all of them in
+    one bucket (eight probes), one only, two neighbours, none, denormals, both signs, the largest
+    numbers; values are the cut points, their neighbours, zeros of both signs, infinities and NaN."""
+    require_gpu()
+    f32 = np.float32
+    one = f32(1.0) + np.arange(253, dtype=f32) * f32(2.0 ** -23)
+    top = np.finfo(f32).max
+    kinds = [np.append(one, f32(1e30)), np.concatenate([[f32(-1e30)], one]), np.array([0.0], f32), np.zeros(0, f32),
+             np.array([1.0, np.nextafter(f32(1.0), f32(2.0))], f32), np.arange(-127, 127, dtype=f32) * f32(1e-40),
+             np.concatenate([-np.geomspace(1e-30, 1e30, 127)[::-1], np.geomspace(1e-30, 1e30, 127)]).astype(f32),
+             np.array([-top, -1.0, 0.0, 1.0, top], f32)]
+    cuts, n_cuts = np.zeros((F, 254), f32), np.zeros(F, np.int32)
+    X = np.zeros((F, rows), f32)
+    rng = np.random.default_rng(rows)
+    for f in range(F):
+        c = kinds[f % len(kinds)]
+        assert (np.diff(c) > 0).all()
+        cuts[f, :c.size], n_cuts[f] = c, c.size
+        with np.errstate(over="ignore"):
+            near = [np.nextafter(c, f32(np.inf)), np.nextafter(c, f32(-np.inf))]
+        vals = np.concatenate([c, *near, np.array([0.0, -0.0, np.inf, -np.inf, np.nan, top, -top, 1e-45], f32)])
+        X[f] = rng.choice(vals, rows)
+    log("gbdt bins of uneven cut points: F=%d rows=%d" % (F, rows))
+    planes = gpu_bin(X, rows, cuts, n_cuts, rows)
+    np.testing.assert_array_equal(from_groups(planes, F, rows), oracle.gbdt_bin(X, rows, cuts, n_cuts, _ld(F))[:, :F])
+
+
 @pytest.mark.parametrize("name,n_prog,s_max,F,depth,p_nan,rounds", [
     ("one-chunk nodes", 300, 8, 20, 6, 0.0, 3),
     ("multi-chunk root, NaN", 1500, 8, 37, 6, 0.2, 2),
