@@ -23,7 +23,7 @@
 //    round sorts its lists; a single one is written out or merged by K5.
 // K4 k_topk_rank: the top k of several sorted lists and the running list by rank computation (an
 //    element's output slot is its own place plus the number of elements of every other list that rank
-//    ahead of it), a workgroup per 1,024 elements.
+//    ahead of it), a workgroup per 256 elements.
 // K5 k_topk_merge: merges one sorted list of this call into the sorted running top-k, likewise.
 #include <hip/hip_runtime.h>
 
@@ -47,6 +47,7 @@ constexpr int kRankSortMax = 128;  // up to this many selected keys are ranked d
 constexpr int kSeg = kSelThreads * kPerThread;  // candidates per workgroup
 constexpr int kMergeThreads = 1024;
 constexpr int kMaxLists = 16, kListKeys = 16384;  // sorted lists k_topk_rank takes, and their keys in LDS
+constexpr int kRankLanes = 4, kRankElems = kMergeThreads / kRankLanes;  // its lanes per element, elements per workgroup
 
 __device__ __forceinline__ uint32_t order_key(float s) {
     uint32_t b = __float_as_uint(s);
@@ -383,22 +384,26 @@ __global__ __launch_bounds__(kMergeThreads) void k_topk_merge(const uint64_t *__
 
 // The top k of up to kMaxLists sorted lists of composites (list q: `counts[q]` of its kk slots) and, with
 // run_score, of the copy of a running top-k: an element's output slot is its place in its own list plus
-// the number of elements ahead of it in every other one, by binary search.  All lists lie in LDS;
-// workgroup b ranks elements [1024 b, 1024 b + 1024) of the lists' slots in turn, then of the running
-// list.  Equal entries cannot meet within the lists, and the running list's come first.
+// the number of elements ahead of it in every other one, by binary search.  All lists lie in LDS.  Four
+// lanes share an element, lane v searching the lists v, v + 4, ..., so that their probes overlap (a lane
+// that searched 16 lists by itself took four chains of probes: 131,072 candidates, k = 129: 30.5 us, 23.5
+// now; 22.9 with a second selection in one workgroup instead).  Workgroup b ranks elements [256 b, 256 b +
+// 256) of the lists' slots in turn, then of the running list.  Equal entries cannot meet within the
+// lists, and the running list's come first.
 __global__ __launch_bounds__(kMergeThreads) void k_topk_rank(const uint64_t *__restrict__ lists,
                                                              const int32_t *__restrict__ counts, int n_lists, int kk,
                                                              const float *__restrict__ score, int n, int64_t index_base,
                                                              const float *__restrict__ run_score,
                                                              const int64_t *__restrict__ run_index, int k,
                                                              float *__restrict__ out_score, int64_t *__restrict__ out_index) {
+    constexpr int U = kMaxLists / kRankLanes;  // lists per lane
     extern __shared__ __align__(16) char smem[];
     __shared__ int cnt[kMaxLists];
     uint64_t *keys = reinterpret_cast<uint64_t *>(smem);                // [n_lists][kk]
     int64_t *ri = reinterpret_cast<int64_t *>(keys + n_lists * kk);     // running list: indices, order keys
     uint32_t *rk = reinterpret_cast<uint32_t *>(ri + k);
-    const int t = threadIdx.x;
-    if (t < n_lists) cnt[t] = min(max(counts[t], 0), kk);
+    const int t = threadIdx.x, sub = t % kRankLanes;
+    if (t < kMaxLists) cnt[t] = t < n_lists ? min(max(counts[t], 0), kk) : 0;
     for (int i0 = t; i0 < n_lists * kk; i0 += 8 * kMergeThreads) {  // eight loads in flight
         uint64_t v[8];
 #pragma unroll
@@ -413,70 +418,69 @@ __global__ __launch_bounds__(kMergeThreads) void k_topk_rank(const uint64_t *__r
             ri[i] = run_index[i];
         }
     __syncthreads();
-    int steps = 0;
-    while ((1 << steps) <= kk) ++steps;  // 2^steps > kk: a search over a list ends within `steps` probes
-    const int per_list = (kk + kMergeThreads - 1) / kMergeThreads;
-    const int own = (int)blockIdx.x / per_list;
+    const int per_list = (kk + kRankElems - 1) / kRankElems;
+    const int own = (int)blockIdx.x / per_list;  // n_lists or more: the running list
+    const int p = (own < n_lists ? (int)blockIdx.x % per_list : (int)blockIdx.x - n_lists * per_list) * kRankElems + t / kRankLanes;
+    if (p >= (own < n_lists ? cnt[own] : k)) return;  // the lanes of an element leave together
+    // this lane's lists: entries of list q ahead of the element
+    int lo[U], hi[U], most = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int q = sub + kRankLanes * u;
+        lo[u] = 0;
+        hi[u] = q != own ? cnt[q] : 0;
+        most = max(most, hi[u]);
+    }
+    uint32_t l = 0;
+    int pos = 0;
     if (own < n_lists) {
-        const int p = (int)blockIdx.x % per_list * kMergeThreads + t;
-        if (p >= cnt[own]) return;
         const uint64_t key = keys[own * kk + p];
-        int pos = p;
-        // four searches at a time: their probes overlap
-        for (int q0 = 0; q0 < n_lists; q0 += 4) {
-            int lo[4], hi[4];
+        while (most > 0) {  // as many probes as the longest of them needs
+            most >>= 1;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int q = q0 + u;
-                lo[u] = 0;
-                hi[u] = q < n_lists && q != own ? cnt[q] : 0;
-            }
-            for (int s = 0; s < steps; ++s)
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (lo[u] < hi[u]) {
-                        const int mid = (lo[u] + hi[u]) >> 1;
-                        if (keys[(q0 + u) * kk + mid] > key) lo[u] = mid + 1;
-                        else hi[u] = mid;
-                    }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) pos += lo[u];
+            for (int u = 0; u < U; ++u)
+                if (lo[u] < hi[u]) {
+                    const int mid = (lo[u] + hi[u]) >> 1;
+                    if (keys[(sub + kRankLanes * u) * kk + mid] > key) lo[u] = mid + 1;
+                    else hi[u] = mid;
+                }
         }
-        uint32_t l = local_of(key);
+        l = local_of(key);
         l = l < (uint32_t)n ? l : (uint32_t)(n - 1);
-        if (run_score) {  // entries ahead of it or equal to it
+        if (run_score && sub == 0) {  // entries ahead of it or equal to it
             const uint32_t kb = (uint32_t)(key >> 32);
             const int64_t ib = index_base + (int64_t)l;
-            int lo = 0, hi = k;
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (!ahead(kb, ib, rk[mid], ri[mid])) lo = mid + 1;
-                else hi = mid;
+            int a = 0, b = k;
+            while (a < b) {
+                const int mid = (a + b) >> 1;
+                if (!ahead(kb, ib, rk[mid], ri[mid])) a = mid + 1;
+                else b = mid;
             }
-            pos += lo;
+            pos = a;
         }
-        if (pos < k) {
-            out_score[pos] = score[l];
-            out_index[pos] = index_base + (int64_t)l;
+    } else {
+        const uint32_t ka = rk[p];
+        const int64_t ia = ri[p];
+        while (most > 0) {  // composites strictly ahead of it
+            most >>= 1;
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (lo[u] < hi[u]) {
+                    const int mid = (lo[u] + hi[u]) >> 1;
+                    const uint64_t c = keys[(sub + kRankLanes * u) * kk + mid];
+                    if (ahead((uint32_t)(c >> 32), index_base + (int64_t)local_of(c), ka, ia)) lo[u] = mid + 1;
+                    else hi[u] = mid;
+                }
         }
-        return;
     }
-    const int i = ((int)blockIdx.x - n_lists * per_list) * kMergeThreads + t;
-    if (i >= k) return;
-    int pos = i;
-    for (int q = 0; q < n_lists && pos < k; ++q) {  // composites strictly ahead of it
-        int lo = 0, hi = cnt[q];
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            const uint64_t c = keys[q * kk + mid];
-            if (ahead((uint32_t)(c >> 32), index_base + (int64_t)local_of(c), rk[i], ri[i])) lo = mid + 1;
-            else hi = mid;
-        }
-        pos += lo;
-    }
-    if (pos < k) {
-        out_score[pos] = run_score[i];
-        out_index[pos] = ri[i];
+#pragma unroll
+    for (int u = 0; u < U; ++u) pos += lo[u];
+#pragma unroll
+    for (int m = 1; m < kRankLanes; m <<= 1) pos += __shfl_xor(pos, m, 64);
+    pos += p;
+    if (sub == 0 && pos < k) {
+        out_score[pos] = own < n_lists ? score[l] : run_score[p];
+        out_index[pos] = own < n_lists ? index_base + (int64_t)l : ri[p];
     }
 }
 
@@ -574,7 +578,7 @@ int topk_launch(const float *score, int32_t n, int32_t k, int64_t index_base, fl
         src = dst;
     }
     if (rank) {
-        const unsigned per = (unsigned)ceil_div(k, kMergeThreads);
+        const unsigned per = (unsigned)ceil_div(k, kRankElems);
         const size_t lds = (size_t)lists * k * 8 + (merge ? (size_t)k * 12 : 0);
         if (const int rc = ensure_dynamic_lds(reinterpret_cast<const void *>(k_topk_rank), lds)) return rc;
         hipLaunchKernelGGL(k_topk_rank, dim3((lists + (merge ? 1 : 0)) * per), dim3(kMergeThreads), lds, stream, src, counts,
