@@ -110,30 +110,38 @@ __global__ __launch_bounds__(kSelThreads) void k_topk_select(const float *__rest
             run.score_copy[i] = run.score[i];
             run.index_copy[i] = run.index[i];
         }
-    uint32_t last_key = 0;
-    int64_t last_index = INT64_MAX;
-    if (FROM_SCORES && RUN) {
-        last_key = order_key(run.score[run.k - 1]);
-        last_index = run.index[run.k - 1];
-    }
-
-    uint64_t x[kPerThread];
+    // register slots j >= jn hold no candidate in any thread: the loops below skip them uniformly
+    const int jn = (n_here + kSelThreads - 1) / kSelThreads;
+    uint64_t x[kPerThread];  // 0: no candidate (padding ranks below every candidate and never enters a histogram)
+    if constexpr (FROM_SCORES && RUN) {
+        float v[kPerThread];  // all loads issued before the running list's last entry is waited for
 #pragma unroll
-    for (int j = 0; j < kPerThread; ++j) {
-        const int64_t i = base + (int64_t)j * kSelThreads + t;
-        x[j] = 0;  // padding ranks below every candidate and never enters a histogram
-        if (i < count) {
-            if constexpr (FROM_SCORES) {
-                const uint32_t key = order_key(score[i]);
-                if (!RUN || ahead(key, run.index_base + i, last_key, last_index))
-                    x[j] = ((uint64_t)key << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)i);
-            } else {
-                x[j] = cin[i];
+        for (int j = 0; j < kPerThread; ++j) {
+            v[j] = 0.f;
+            if (j < jn) v[j] = score[base + min(j * kSelThreads + t, n_here - 1)];
+        }
+        const uint32_t last_key = order_key(run.score[run.k - 1]);
+        const int64_t last_index = run.index[run.k - 1];
+#pragma unroll
+        for (int j = 0; j < kPerThread; ++j) {
+            const int64_t i = base + (int64_t)j * kSelThreads + t;
+            const uint32_t key = order_key(v[j]);
+            const bool in = i < count && ahead(key, run.index_base + i, last_key, last_index);
+            x[j] = in ? ((uint64_t)key << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)i) : 0;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < kPerThread; ++j) {
+            const int64_t i = base + (int64_t)j * kSelThreads + t;
+            x[j] = 0;
+            if (i < count) {
+                if constexpr (FROM_SCORES)
+                    x[j] = ((uint64_t)order_key(score[i]) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)i);
+                else
+                    x[j] = cin[i];
             }
         }
     }
-    // register slots j >= jn hold no candidate in any thread: the loops below skip them uniformly
-    const int jn = (n_here + kSelThreads - 1) / kSelThreads;
     auto valid = [&](int j) { return RUN ? x[j] != 0 : j * kSelThreads + t < n_here; };  // no candidate's composite is 0
     if constexpr (RUN) {  // candidates were dropped: count the others
         uint32_t mine = 0;
@@ -344,11 +352,13 @@ __global__ __launch_bounds__(kMergeThreads) void k_topk_merge(const uint64_t *__
         ak[i] = order_key(as[i]);
         ai[i] = io_index[i];
     }
-    for (int j = threadIdx.x; j < nb; j += kMergeThreads) {
-        uint32_t l = local_of(bkeys[j]);
+    for (int j = threadIdx.x; j < min(k, n); j += kMergeThreads) {  // not nb: no load waits for the count
+        const uint64_t key = bkeys[j];
+        if (key == 0) continue;  // the slots past the list's candidates
+        uint32_t l = local_of(key);
         l = l < (uint32_t)n ? l : (uint32_t)(n - 1);
         bs[j] = score[l];
-        bk[j] = (uint32_t)(bkeys[j] >> 32);
+        bk[j] = (uint32_t)(key >> 32);
         bi[j] = index_base + (int64_t)l;
     }
     __syncthreads();
@@ -531,9 +541,10 @@ int topk_launch(const float *score, int32_t n, int32_t k, int64_t index_base, fl
     const bool merge = flags & HARL_TOPK_MERGE;
     int32_t *counts = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + 2 * buf_bytes);  // kMaxLists words
     // Rounds until the segments are few enough lists for k_topk_rank (sorted once, in parallel) or one.
-    // 65,536 candidates, k = 1,024: selection 12.5 us, a second round in one workgroup 19 us and a
-    // merge 4 us before; now selection with sort 17 us and ranking 7 us, and against a running list
-    // that drops most candidates at the load 7 + 6 us.
+    // 65,536 candidates, k = 1,024, into an empty running list 38.4 us with a second round in one workgroup
+    // and a merge, 32.0 with one round and ranking; into a full one, which drops most candidates at the
+    // load, 36.5 and 10.9 us.  With k = 129 in 16 lists, the worst of them, 22.9 and 23.3 (no list), 27.0 and
+    // 26.5 (empty).
     const int64_t max_lists = std::min<int64_t>(kMaxLists, kListKeys / k);
     int rounds = 0;
     while (rounds + 1 < p.rounds && ceil_div(p.counts[rounds], kSeg) > max_lists) ++rounds;
