@@ -220,10 +220,9 @@ __global__ __launch_bounds__(kGemmThreads) void k_gemm(GemmArgs g) {
 // = l / 16 holds k = 16 c + 4 q + u for MFMA u of chunk c, the same for A and B, and a wave needs
 // (TI + TJ) / 32 reads for TI TJ / 256 MFMAs.  The row stride of TK + 4 floats spreads 16 rows' reads
 // over all banks.  An operand that is contiguous along its rows is loaded 8 K values x 8 groups of
-// rows (128-byte lines) per wave and transposed by four 4-byte LDS stores per lane.  Before, every
-// MFMA took two 4-byte LDS reads, row tiles were 64 at most, heads of 27 columns took 64, and tiles
-// that share an operand lay on different XCDs: an update of 65,536 transitions took 595 us and then
-// 512, of 4,096 transitions 99.5 us and then 95.8.
+// rows (128-byte lines) per wave and transposed by four 4-byte LDS stores per lane.  An update
+// of 65,536 transitions (64-256-256 -> 26) takes 480 us, with k_gemm's reads and tiles alone 595; of 4,096
+// transitions 92 and 99.5.
 template <int T, int TK>
 __device__ __forceinline__ void stage_at(bool row_fast, int e, int &row, int &k) {
     if (row_fast) {
@@ -375,8 +374,6 @@ __global__ __launch_bounds__(256) void k_split_sum(const float *__restrict__ par
         out[r * (J - 1) + c] = s;
     }
 }
-
-// Column sums of Y [rows][J] (row stride ldy), each row weighted by w[row] when w is given:
 
 struct HeadArgs {
     const float *logits, *logp_old, *adv, *ret;

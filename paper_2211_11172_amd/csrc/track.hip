@@ -411,27 +411,10 @@ __global__ __launch_bounds__(kFusedThreads) void k_elim_fused(const float *__res
         // the other histogram was last read before the previous pass's final barrier
         if (t < 256) hist[hb ^ 1][t] = 0;
         __syncthreads();
-        if (t < 64) {
-            const uint32_t *h = hist[hb];
-            const uint32_t h0 = h[255 - 4 * t], h1 = h[254 - 4 * t], h2 = h[253 - 4 * t], h3 = h[252 - 4 * t];
-            const uint32_t sum = h0 + h1 + h2 + h3;
-            uint32_t incl = sum;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const uint32_t v = __shfl_up(incl, o, 64);
-                if (t >= o) incl += v;
-            }
-            const uint32_t excl = incl - sum;
-            if (excl < need && incl >= need) {
-                uint32_t above = excl;
-                int d;
-                if (above + h0 >= need) d = 255 - 4 * t;
-                else if (above += h0, above + h1 >= need) d = 254 - 4 * t;
-                else if (above += h1, above + h2 >= need) d = 253 - 4 * t;
-                else { above += h2; d = 252 - 4 * t; }
-                s_digit = (uint32_t)d;
-                s_above = above;
-            }
+        uint32_t d, above;
+        if (t < 64 && pick_digit(hist[hb], need, d, above)) {
+            s_digit = d;
+            s_above = above;
         }
         __syncthreads();
         prefix |= s_digit << shift;
