@@ -14,7 +14,7 @@
 //                   of 64-bit integers are exact, and no result depends on summation order; each
 //                   statement row's integer gradient and hessian
 //   per depth d < max_depth (rows kept grouped by node in `order`, the root in row order):
-//     k_gb_segments (before d = 1, large sets) bins and gradient pairs as one line per row
+//     k_gb_segments (before d = 1, some large sets) bins and gradient pairs as lines of a row
 //     k_gb_hist     workgroup = (chunk of a node's rows, 8 features): a [2][8][256] int64 histogram
 //                   in LDS (ds_add of integers; the lanes of one add instruction are spread over the
 //                   8 features, so at most 8 meet on one bin; the bin of 0.0 is the total minus the
@@ -27,21 +27,20 @@
 //                   its rows moved to the children's ranges, or the leaf's weight added to their
 //                   margins
 //
-// What bounds it, on 2.12 M rows x 164 features (two rounds with binning: 15.4 -> 4.1 ms): the
-// root's histogram (205 us) by its LDS adds and by reading 8 B of bins and, per feature group, 16 B
-// of gradient pair a row (148 us without the adds); the levels below it, when every node was built
-// from 8-byte gathers, by cache lines of which a sparse node uses 8 of 128 bytes (600 us a level).
-// Building the smaller child alone halves the rows and more (this data: 0.8 M .. 0.02 M of 2.1 M);
-// the line layout makes a row cost two lines instead of 21 + 1 (650 K rows in 4 nodes: 334 -> 150
-// us) for one 170 us pass.  On 68,182 rows (four rounds: 2.73 -> 1.6 ms) launches and chains of
-// dependent loads bound it: three launches a level instead of nine, each level's work list worked
-// out by every workgroup for itself.
+// What bounds it, on 2.12 M rows x 164 features (binning + two rounds: 14.5 -> 3.7 ms; one round's
+// k_gb_hist 5.2 -> 0.90 ms): the root's histogram (205 us) by its LDS adds and by reading 8 B of bins and,
+// per feature group, 16 B of gradient pair a row; the levels below it (150 .. 42 us; 520 us a level on
+// average when every node was built from 8-byte gathers) by cache lines and LDS adds.  Building the smaller child alone
+// halves the rows and more; the line layout (169 us, once) makes a row cost two lines instead of 21 + 1.
+// On 68,182 rows (binning + four rounds: 2.74 -> 1.60 ms) launches and chains of dependent loads bound it:
+// three launches a level instead of nine, each level's work list worked out by every workgroup for
+// itself.
 //
-// Split evaluation (thread = (feature, 8 consecutive bins)): an int64 prefix over bins gives GL,
-// HL for every threshold index t; the gain GL^2/(HL+l) + GR^2/(HR+l) - G^2/(H+l) is fp64 with
-// contraction off, missing rows tried left, then right; the best is the largest gain, ties to the
-// lowest (feature, t, missing-left first).  Every decision is therefore bit-identical to a
-// sequential evaluation of the same definitions.
+// Split evaluation (k_gb_hist in place: thread = (feature, 8 consecutive bins); k_gb_split: thread = bin):
+// an int64 prefix over bins gives GL, HL for every threshold index t; the gain GL^2/(HL+l) + GR^2/(HR+l) -
+// G^2/(H+l) is fp64 with contraction off, missing rows tried left, then right (without missing rows both
+// are one split); the best is the largest gain, ties to the lowest (feature, t, missing-left first).
+// Every decision is therefore bit-identical to a sequential evaluation of the same definitions.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -186,7 +185,7 @@ __device__ __forceinline__ void best_lanes(int &bv, double &bg, int &bk, int64_t
 // same for cut points and values, so the result is the plain count of cut points <= x; -0 counts as +0.
 // A thread codes two rows of the group, whose 16 searches overlap; the first rows are loaded while the
 // table is built, which 32 lanes per feature do by counting (1 us; a search per bucket took 9).
-// 2.1 M rows x 164 features: 760 us with searches over all cut points (8 probes), 400 us now, 4.3 TB/s of
+// 2.1 M rows x 164 features: 760 us with searches over all cut points (8 probes), 402 us now, 4.3 TB/s of
 // the features and bins; the probes' LDS reads and the address arithmetic bound it.  16,384 rows x 164
 // features: 10.3 us then, 10.7 now.
 __device__ __forceinline__ uint32_t bin_key(float v) {
