@@ -27,12 +27,12 @@
 //                   its rows moved to the children's ranges, or the leaf's weight added to their
 //                   margins
 //
-// What bounds it, on 2.12 M rows x 164 features (binning + two rounds: 14.5 -> 3.7 ms; one round's
+// What bounds it, on 2.12 M rows x 164 features (binning + two rounds: 14.9 -> 3.7 ms; one round's
 // k_gb_hist 5.2 -> 0.90 ms): the root's histogram (205 us) by its LDS adds and by reading 8 B of bins and,
 // per feature group, 16 B of gradient pair a row; the levels below it (150 .. 42 us; 520 us a level on
 // average when every node was built from 8-byte gathers) by cache lines and LDS adds.  Building the smaller child alone
 // halves the rows and more; the line layout (169 us, once) makes a row cost two lines instead of 21 + 1.
-// On 68,182 rows (binning + four rounds: 2.74 -> 1.60 ms) launches and chains of dependent loads bound it:
+// On 68,182 rows (binning + four rounds: 2.76 -> 1.6 ms) launches and chains of dependent loads bound it:
 // three launches a level instead of nine, each level's work list worked out by every workgroup for
 // itself.
 //

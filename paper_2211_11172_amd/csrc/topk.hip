@@ -398,7 +398,7 @@ __global__ __launch_bounds__(kMergeThreads) void k_topk_merge(const uint64_t *__
 // run_score, of the copy of a running top-k: an element's output slot is its place in its own list plus
 // the number of elements ahead of it in every other one, by binary search.  All lists lie in LDS.  Four
 // lanes share an element, lane v searching the lists v, v + 4, ..., so that their probes overlap (a lane
-// that searched 16 lists by itself took four chains of probes: 131,072 candidates, k = 129: 30.5 us, 23.5
+// that searched 16 lists by itself took four chains of probes: 131,072 candidates, k = 129: 30.4 us, 23.1
 // now; 22.9 with a second selection in one workgroup instead).  Workgroup b ranks elements [256 b, 256 b +
 // 256) of the lists' slots in turn, then of the running list.  Equal entries cannot meet within the
 // lists, and the running list's come first.
@@ -543,10 +543,10 @@ int topk_launch(const float *score, int32_t n, int32_t k, int64_t index_base, fl
     const bool merge = flags & HARL_TOPK_MERGE;
     int32_t *counts = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + 2 * buf_bytes);  // kMaxLists words
     // Rounds until the segments are few enough lists for k_topk_rank (sorted once, in parallel) or one.
-    // 65,536 candidates, k = 1,024, into an empty running list 38.4 us with a second round in one workgroup
-    // and a merge, 32.0 with one round and ranking; into a full one, which drops most candidates at the
-    // load, 36.5 and 10.9 us.  With k = 129 in 16 lists, the worst of them, 22.9 and 23.3 (no list), 27.0 and
-    // 26.5 (empty).
+    // 65,536 candidates, k = 1,024, into an empty running list 38.3 us with a second round in one workgroup
+    // and a merge, 31.2 with one round and ranking; into a full one, which drops most candidates at the
+    // load, 36.4 and 10.9 us.  With k = 129 in 16 lists, the worst of them, 22.9 and 23.1 (no list), 27.0 and
+    // 26.0 (empty).
     const int64_t max_lists = std::min<int64_t>(kMaxLists, kListKeys / k);
     int rounds = 0;
     while (rounds + 1 < p.rounds && ceil_div(p.counts[rounds], kSeg) > max_lists) ++rounds;
